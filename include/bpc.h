@@ -134,16 +134,19 @@ int bpc_decode_path_taken(int B, int Hq, int Hkv, int N, int L);
  *           decisions is ADDED (the caller zeroes it), or NULL
  * workspace    device memory of at least bpc_build_workspace_bytes(...)
  *           bytes, 256-byte aligned; its contents on entry do not matter.
- * Cost: 2 L + 2 kernel launches.  With that workspace nothing of size N x D
- * is stored: each bit's pass recomputes R_j from the bf16 key, the key's
- * code bits so far and P (the same rounded subtractions, in the same
- * order), so the workspace holds one fp64 partial sum per 128-key chunk
- * and coordinate plus fp64 copies of P and G.  Given at least
- * bpc_build_checkpoint_workspace_bytes(...) bytes (1 KiB more per key,
- * rounded up to 128-key chunks), the build also keeps each key's fp64
- * residual there every 16 bits and later passes start from it, trading
- * that memory and its traffic for fewer recomputed subtractions; the
- * results are bit for bit the same.
+ * Cost: 2 L + 4 kernel launches.  Nothing of size N x D is stored and no
+ * residual is formed: with bpc_build_workspace_bytes(...) bytes each bit is one
+ * pass over the bf16 keys, in which a_j and sum_j u_j R_j come from unrolled
+ * sums, every sign and every entry of P certified to be the one the arithmetic
+ * above gives, or computed in that arithmetic; the results are bit for bit
+ * those.  The workspace then holds the codes as bit planes (L / 8 bytes per
+ * key), 2 bytes per key and per-workgroup sums.  A smaller workspace, down to
+ * one fp64 partial sum per 128-key chunk and coordinate plus fp64 copies of P
+ * and G, is accepted as well: each pass then recomputes every R_j from the
+ * key, its code bits so far and P, with the same results.
+ * bpc_build_checkpoint_workspace_bytes gives 1 KiB more per key (the size of
+ * an fp64 residual, rounded up to 128-key chunks); it is accepted like any
+ * larger workspace and no longer makes a difference.
  */
 size_t bpc_build_workspace_bytes(int B, int Hkv, int N, int D, int L);
 size_t bpc_build_checkpoint_workspace_bytes(int B, int Hkv, int N, int D, int L);

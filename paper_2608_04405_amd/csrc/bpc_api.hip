@@ -112,21 +112,41 @@ DecodeLayout decode_layout(int B, int Hq, int Hkv, int N, int L, int k) {
 BuildLayout build_layout(int B, int Hkv, int N, int L) {
   BuildLayout b{};
   const size_t BH = (size_t)B * Hkv;
-  b.nchunks = (N + kBuildChunk - 1) / kBuildChunk;
   size_t o = 0;
-  b.off_part = o;  // one fp64 tree sum per chunk and coordinate
-  o = align_up(o + BH * b.nchunks * (size_t)kHeadDim * sizeof(double), 256);
+  auto take = [&](size_t bytes) {
+    size_t at = o;
+    o = align_up(o + bytes, 256);
+    return at;
+  };
+  b.off_p64 = take(BH * (size_t)L * kHeadDim * sizeof(double));  // P widened to fp64
+  const size_t shared = o;
+  b.nchunks = (N + kBuildChunk - 1) / kBuildChunk;
+  b.off_part = take(BH * b.nchunks * (size_t)kHeadDim * sizeof(double));  // one fp64 tree sum per chunk and coordinate
   b.nfold = b.nchunks > 8 * kBuildFold ? (b.nchunks + kBuildFold - 1) / kBuildFold : 0;
-  b.off_fold = o;  // one fp64 tree sum per block of chunks and coordinate
-  o = align_up(o + BH * b.nfold * (size_t)kHeadDim * sizeof(double), 256);
-  b.off_p64 = o;   // P widened to fp64, the scalar operand of the residual
-  o = align_up(o + BH * (size_t)L * kHeadDim * sizeof(double), 256);
-  b.off_g64 = o;   // G widened to fp64
-  o = align_up(o + (size_t)L * kHeadDim * sizeof(double), 256);
-  b.total = o;
-  b.off_ck = o;    // fp64 residual of every key, padded to whole chunks
-  o = align_up(o + BH * b.nchunks * (size_t)kBuildChunk * kHeadDim * sizeof(double), 256);
-  b.total_ck = o;
+  b.off_fold = take(BH * b.nfold * (size_t)kHeadDim * sizeof(double));  // and per block of chunks
+  b.off_g64 = take((size_t)L * kHeadDim * sizeof(double));              // G widened to fp64
+  b.total_min = o;
+
+  o = shared;
+  const size_t nblk = ((size_t)N + 63) / 64;
+  // two workgroups per compute unit, all resident at once, while that leaves
+  // each wavefront a block
+  const size_t want = (BH * nblk + kScanWgs - 1) / kScanWgs;
+  b.scan_blocks = (int)(want <= 4 ? 4 : (want + 3) / 4 * 4);
+  b.scan_wgs = (int)((nblk + b.scan_blocks - 1) / b.scan_blocks);
+  const size_t wgs = BH * b.scan_wgs;
+  b.off_psum = take(wgs * kHeadDim * sizeof(double));            // per workgroup sum_j u_j k_j
+  b.off_pcnt = take(wgs * kHeadDim * sizeof(uint32_t));          // and popcounts against the earlier bits
+  b.off_node = take(BH * 2 * (size_t)b.nchunks * sizeof(double));  // a column's tree over chunks
+  b.off_planes = take(BH * nblk * (size_t)L * sizeof(uint64_t));  // the codes as bit planes of 64 keys
+  b.off_knorm = take(BH * (size_t)N * sizeof(uint16_t));         // per key a bound of |k|
+  b.off_stat = take(BH * kScanStats * kHeadDim * sizeof(double));
+  b.off_cmat = take(BH * (size_t)L * L * sizeof(double));        // P_t . g_s, t < s
+  b.off_corr = take(BH * (size_t)L * sizeof(double));
+  b.off_tab = take(BH * (size_t)(L / 8) * 256 * sizeof(float));
+  b.off_bound = take(BH * 4 * sizeof(float));
+  b.total = o > b.total_min ? o : b.total_min;
+  b.total_ck = align_up(b.total + BH * b.nchunks * (size_t)kBuildChunk * kHeadDim * sizeof(double), 256);
   return b;
 }
 
@@ -201,14 +221,13 @@ int bpc_build_hash(const uint16_t* K, int64_t sK_b, int64_t sK_h, int64_t sK_n, 
   if ((st = check_codes("codes_out", codes_out, sC_b, sC_h, L / 32))) return st;
   if ((st = check_opt_aligned("err_out", err_out))) return st;
   const BuildLayout lay = build_layout(B, Hkv, N, L);
-  if (!workspace || workspace_bytes < lay.total)
+  if (!workspace || workspace_bytes < lay.total_min)
     return fail(BPC_EWORKSPACE, "workspace of %zu bytes given, %zu needed", workspace ? workspace_bytes : 0,
-                lay.total);
+                lay.total_min);
   if (reinterpret_cast<uintptr_t>(workspace) & 255u) return fail(BPC_EALIGN, "workspace must be 256-byte aligned");
-  const bool checkpoint = workspace_bytes >= lay.total_ck;
-  hipError_t e = launch_build(K, sK_b, sK_h, sK_n, B, Hkv, N, L, G, P_out, codes_out, sC_b, sC_h, err_out,
-                              fragile_out, static_cast<char*>(workspace), checkpoint,
-                              static_cast<hipStream_t>(stream));
+  const BuildArgs a{K, sK_b, sK_h, sK_n, B, Hkv, N, L, G, P_out, codes_out, sC_b, sC_h, err_out, fragile_out,
+                    static_cast<char*>(workspace), static_cast<hipStream_t>(stream)};
+  hipError_t e = launch_build(a, workspace_bytes >= lay.total);
   if (e != hipSuccess) return hip_fail(e, "bpc_build_hash launch");
   return BPC_OK;
 }

@@ -73,14 +73,12 @@ constexpr size_t kSyncRegionBytes = kSyncCounterBytes + (size_t)kFusedMaxBH * kF
 constexpr int kBuildGroups = 2;                  // groups of 64 keys per build workgroup
 constexpr int kBuildThreads = 256 * kBuildGroups;  // four wavefronts (coordinate blocks) per group
 constexpr int kBuildChunk = 64 * kBuildGroups;     // keys per workgroup (one chunk of the row tree)
-#ifndef BPC_BUILD_CKPT_PERIOD
-#define BPC_BUILD_CKPT_PERIOD 16
-#endif
-// bits between stored fp64 residuals when the build keeps a checkpoint
-constexpr int kBuildCkptPeriod = BPC_BUILD_CKPT_PERIOD;
 // chunk sums folded per workgroup before the per-(b, h) reduction, when a
 // (b, h) has more than 8 such blocks of chunks
 constexpr int kBuildFold = 32;
+// fp64 values per (b, h) and coordinate that the scanning build carries from bit to bit
+constexpr int kScanStats = 7;
+constexpr int kScanWgs = 512;  // workgroups of one of its passes: two per compute unit, all resident
 
 // ---- workspace layouts -----------------------------------------------------
 // Decode, per slice sl = (b Hkv + h) nslices + s: candidates [kSlice] u32
@@ -110,8 +108,13 @@ struct DecodeLayout {
 struct BuildLayout {
   int nchunks;
   int nfold;  // aligned blocks of kBuildFold chunks folded first, or 0
-  size_t off_part, off_fold, off_p64, off_g64, total;
-  size_t off_ck, total_ck;  // the residual checkpoint, when the workspace holds one
+  // the recomputing build: needs the least memory
+  size_t off_part, off_fold, off_p64, off_g64, total_min;
+  // the scanning build (P64 shared with the above): workgroups per (b, h) and
+  // 64-key blocks per workgroup of its passes
+  int scan_wgs, scan_blocks;
+  size_t off_psum, off_pcnt, off_node, off_planes, off_knorm, off_stat, off_cmat, off_corr, off_tab, off_bound, total;
+  size_t total_ck;  // with the room of an fp64 residual per key, which no build needs any more
 };
 
 DecodeLayout decode_layout(int B, int Hq, int Hkv, int N, int L, int k);
@@ -192,10 +195,23 @@ hipError_t launch_hash_mm(const uint16_t* K, int64_t sK_b, int64_t sK_h, int64_t
                           const float* P, int64_t sP_b, int64_t sP_h, uint32_t* codes, int64_t sC_b, int64_t sC_h,
                           unsigned long long* fragile, unsigned long long* fallbacks, hipStream_t stream);
 
-hipError_t launch_build(const uint16_t* K, int64_t sK_b, int64_t sK_h, int64_t sK_n, int B, int Hkv,
-                        int N, int L, const float* G, float* P, uint32_t* codes, int64_t sC_b,
-                        int64_t sC_h, float* err, unsigned long long* fragile, char* ws,
-                        bool checkpoint, hipStream_t stream);
+struct BuildArgs {
+  const uint16_t* K;
+  int64_t sK_b, sK_h, sK_n;
+  int B, Hkv, N, L;
+  const float* G;
+  float* P;
+  uint32_t* codes;
+  int64_t sC_b, sC_h;
+  float* err;
+  unsigned long long* fragile;
+  char* ws;
+  hipStream_t stream;
+};
+// scan: the workspace holds BuildLayout::total bytes (else total_min)
+hipError_t launch_build(const BuildArgs& a, bool scan);
+// the scanning build of P (and its fp64 widening) and the codes
+void launch_build_scan(const BuildArgs& a, const BuildLayout& lay);
 
 // ---- device helpers ----------------------------------------------------------
 __device__ __forceinline__ double bf16_to_f64(uint16_t b) {

@@ -1,0 +1,765 @@
+// Algorithm 1 ("Constructing hash codes and corresponding hashing
+// projection", Sec. 3.2) without the residuals: the results of the
+// fixed-order fp64 build, bit for bit, from one read of the bf16 keys per bit.
+//
+// With R_j = k_j - sum_{t<i} u_jt P_t, both things bit i needs unroll:
+//
+//   a_j = R_j . g_i = k_j . g_i - sum_{t<i} u_jt (P_t . g_i)
+//   s   = sum_j u_ji R_j = sum_j u_ji k_j - sum_{t<i} n_it P_t,
+//         n_it = sum_j u_ji u_jt = N - 2 popcount(column i ^ column t),
+//
+// so a pass reads each key once (256 bytes) plus its code words, and the
+// L x D fused subtractions per key of a rebuilt residual (or its 1 KiB of
+// fp64 checkpoint) never happen.  Neither value is the fixed-order one, so
+// both are certified:
+//
+// Signs, in three tiers.  (1) k_j . g_i on the matrix cores (bf16 keys times
+// g cut exactly into three bf16 parts, fp32 accumulation), the corrections
+// from fp32 tables of the partial sums over each code byte.  The distance to
+// the fixed-order value is at most |k| alpha1 + beta1 (build_solve_kernel).
+// (2) A decision inside that bound (about one in a thousand) is taken again in
+// fp64, with the bound |k| alpha2 + beta2; both betas hold the threshold of a
+// fragile decision.  (3) What is still inside (the fragile decisions and a few
+// more) is decided in the reference arithmetic itself.
+//
+// P: |s - (the pairwise-tree sum)| <= B per coordinate, from the energy of
+// the residual, E_d = sum_j R_jd^2, which is known without the residual
+// (E' = E - 2 p s + N p^2) and bounds sum_j |R_jd| by sqrt(N E_d).  When
+// (float)((s - B) / N) and (float)((s + B) / N) are the same bits, that is
+// P[i][d]; otherwise (about one (b, h) and bit in several hundred) the
+// column's tree is summed in the reference order.  Zero columns, non-finite
+// keys and exactly cancelling sums never certify and take the exact route.
+
+#pragma clang fp contract(off)
+
+#include "bpc_internal.h"
+#include "mfma_split.h"
+
+namespace bpc {
+
+constexpr int kScanThreads = 256;
+constexpr double kEps = 0x1p-53;
+
+typedef uint16_t u16x2_t __attribute__((ext_vector_type(2)));
+
+// One reduce-scatter level over the 16 lanes of a row: lane l and its partner
+// (CTRL: row mirror, half mirror, or a quad permutation) add their halves of
+// the 2 * HALF values they carry; the lane with bit BIT set keeps the upper half.
+template <int CTRL, int BIT, int HALF>
+__device__ __forceinline__ void row_reduce_level(double (&v)[32], int lane) {
+  const bool upper = (lane >> BIT) & 1;
+#pragma unroll
+  for (int e = 0; e < HALF; ++e) {
+    const double send = upper ? v[e] : v[HALF + e];
+    const double keep = upper ? v[HALF + e] : v[e];
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(send), CTRL, 0xF, 0xF, false);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(send), CTRL, 0xF, 0xF, false);
+    v[e] = keep + __hiloint2double(hi, lo);
+  }
+}
+// the sums over the row of 32 values per lane: afterwards v[0] and v[1] of lane
+// l are those of the values row_reduce_index(l) and the next
+__device__ __forceinline__ void row_reduce(double (&v)[32], int lane) {
+  row_reduce_level<0x140, 3, 16>(v, lane);  // row_mirror: l and 15 - l
+  row_reduce_level<0x141, 2, 8>(v, lane);   // row_half_mirror
+  row_reduce_level<0x4E, 1, 4>(v, lane);    // quad_perm [2, 3, 0, 1]
+  row_reduce_level<0xB1, 0, 2>(v, lane);    // quad_perm [1, 0, 3, 2]
+}
+__device__ __forceinline__ int row_reduce_index(int lane) { return 2 * (lane & 15); }
+
+// A 64-key tile of a wavefront in matrix-core operand order: lane (c16, g4)
+// holds, of key base + 16 tau + c16, the coordinates 32 m + 8 g4 .. + 7 in
+// kv[tau][m]; keys past N are zero.  row_bytes < 2^25, so that an offset within
+// the tile fits 32 bits.
+__device__ __forceinline__ void load_tile(const uint16_t* Kb, uint32_t row_bytes, int base, int N, int c16, int g4,
+                                          uint4 (&kv)[4][4]) {
+  const char* tile = reinterpret_cast<const char*>(Kb) + (uint64_t)base * row_bytes;  // the same in every lane
+#pragma unroll
+  for (int tau = 0; tau < 4; ++tau) {
+    const uint32_t off = (uint32_t)min(16 * tau + c16, N - 1 - base) * row_bytes + 16u * g4;
+#pragma unroll
+    for (int m = 0; m < 4; ++m) kv[tau][m] = *reinterpret_cast<const uint4*>(tile + (off + 64u * m));
+  }
+  if (base + 64 > N) {
+#pragma unroll
+    for (int tau = 0; tau < 4; ++tau)
+#pragma unroll
+      for (int m = 0; m < 4; ++m)
+        if (base + 16 * tau + c16 >= N) kv[tau][m] = make_uint4(0u, 0u, 0u, 0u);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Per (b, h) and coordinate: sum k^2 (psum), the largest and smallest nonzero
+// magnitude (pext: max in the low half, min in the high half; bit 15 of the
+// low half: a sign bit was seen, in an all-zero column a negative zero); per key an upper bound of |k| as bf16.
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(kScanThreads, 2) void build_stat_kernel(const uint16_t* __restrict__ K, int64_t sK_b,
+                                                                     int64_t sK_h, int64_t sK_n, int Hkv, int N,
+                                                                     int blocks_per_wg, double* __restrict__ psum,
+                                                                     uint32_t* __restrict__ pext,
+                                                                     uint16_t* __restrict__ knorm, int nblk) {
+  __shared__ double red[4][kHeadDim];
+  __shared__ uint32_t ext[kHeadDim][3];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int c16 = lane & 15, g4 = lane >> 4;
+  const int bh = blockIdx.y, b = bh / Hkv, h = bh % Hkv;
+  const uint16_t* Kb = K + b * sK_b + h * sK_h;
+  const uint32_t row_bytes = (uint32_t)sK_n * 2u;
+  for (int e = tid; e < kHeadDim; e += kScanThreads) ext[e][0] = 0u, ext[e][1] = 0x7FFFu, ext[e][2] = 0u;
+  __syncthreads();
+  // two coordinates per word: the largest magnitude, the smallest magnitude
+  // minus one (so that zeros count as the largest), the bits seen
+  double acc[32];
+  u16x2_t mx[16], mn[16];
+  uint32_t seen[16];
+#pragma unroll
+  for (int e = 0; e < 32; ++e) acc[e] = 0.0;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) mx[e] = (u16x2_t){0, 0}, mn[e] = (u16x2_t){0xFFFF, 0xFFFF}, seen[e] = 0u;
+  const int blk_end = min((int)(blockIdx.x + 1) * blocks_per_wg, nblk);
+  for (int blk = blockIdx.x * blocks_per_wg + wave; blk < blk_end; blk += 4) {
+    uint4 kv[4][4];
+    load_tile(Kb, row_bytes, __builtin_amdgcn_readfirstlane(blk * 64), N, c16, g4, kv);
+    float ss[4];
+#pragma unroll
+    for (int tau = 0; tau < 4; ++tau) {
+      ss[tau] = 0.f;
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {
+        const uint32_t wd[4] = {kv[tau][m].x, kv[tau][m].y, kv[tau][m].z, kv[tau][m].w};
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+          const float f0 = __uint_as_float(wd[w] << 16), f1 = __uint_as_float(wd[w] & 0xFFFF0000u);
+          acc[8 * m + 2 * w] = __builtin_fma((double)f0, (double)f0, acc[8 * m + 2 * w]);
+          acc[8 * m + 2 * w + 1] = __builtin_fma((double)f1, (double)f1, acc[8 * m + 2 * w + 1]);
+          ss[tau] = fmaf(f1, f1, fmaf(f0, f0, ss[tau]));
+          const u16x2_t mag = __builtin_bit_cast(u16x2_t, wd[w] & 0x7FFF7FFFu);
+          mx[4 * m + w] = __builtin_elementwise_max(mx[4 * m + w], mag);
+          mn[4 * m + w] = __builtin_elementwise_min(mn[4 * m + w], (u16x2_t)(mag - (u16x2_t){1, 1}));
+          seen[4 * m + w] |= wd[w];
+        }
+      }
+      ss[tau] += __shfl_xor(ss[tau], 16, 64);
+      ss[tau] += __shfl_xor(ss[tau], 32, 64);
+    }
+    // lane l: the key base + l; rounded up (the sum's own roundings, squares
+    // below 2^-126, the cut to bf16)
+    const float s = g4 == 0 ? ss[0] : g4 == 1 ? ss[1] : g4 == 2 ? ss[2] : ss[3];
+    const float nk = sqrtf(s * (1.f + 0x1p-14f)) * (1.f + 0x1p-20f) + 0x1p-55f;
+    const uint32_t nb = __float_as_uint(nk);
+    // (infinity and NaN keep their class: the cut below adds no carry into them)
+    const uint32_t up = nk < 3e38f ? (nb + 0xFFFFu) >> 16 : (nk == nk ? 0x7F80u : 0x7FC0u);
+    if (blk * 64 + lane < N) knorm[(size_t)bh * N + blk * 64 + lane] = (uint16_t)up;
+  }
+#pragma unroll
+  for (int e = 0; e < 32; ++e) {
+    const int d = 32 * (e >> 3) + 8 * g4 + (e & 7);
+    atomicMax(&ext[d][0], (uint32_t)mx[e >> 1][e & 1]);
+    atomicMin(&ext[d][1], min((uint32_t)(uint16_t)mn[e >> 1][e & 1] + 1u, 0x7FFFu));
+    if ((seen[e >> 1] >> (16 * (e & 1))) & 0x8000u) atomicOr(&ext[d][2], 1u);
+  }
+  row_reduce(acc, lane);
+  const int e0 = row_reduce_index(lane);
+#pragma unroll
+  for (int x = 0; x < 2; ++x) red[wave][32 * (e0 >> 3) + 8 * g4 + (e0 & 7) + x] = acc[x];
+  __syncthreads();
+  if (tid < kHeadDim) {
+    const size_t at = ((size_t)bh * gridDim.x + blockIdx.x) * kHeadDim + tid;
+    psum[at] = (red[0][tid] + red[1][tid]) + (red[2][tid] + red[3][tid]);
+    pext[at] = (ext[tid][0] | (ext[tid][2] << 15)) | (ext[tid][1] << 16);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Decision `bit` of one key in the reference arithmetic, by the whole
+// wavefront: lane l rebuilds coordinates l and l + 64 with one rounded
+// subtraction per earlier bit, the products are rounded, each block of 32
+// coordinates is summed in ascending order from +0 and the blocks combined as
+// ((b0 + b1) + (b2 + b3)).
+// ---------------------------------------------------------------------------
+template <int W>
+__device__ __forceinline__ double reference_decision(const uint16_t* krow, const float* Pb, const float* g, int bit,
+                                                     const uint32_t (&cw)[W], double* fb) {
+  const int l = threadIdx.x & 63;
+  double r0 = bf16_to_f64(krow[l]), r1 = bf16_to_f64(krow[l + 64]);
+#pragma unroll
+  for (int w = 0; w < W; ++w) {
+    for (int t = 32 * w; t < min(bit, 32 * w + 32); ++t) {
+      const double p0 = (double)Pb[t * kHeadDim + l], p1 = (double)Pb[t * kHeadDim + l + 64];
+      const double sg = ((cw[w] >> (t & 31)) & 1u) ? -1.0 : 1.0;
+      r0 = __builtin_fma(sg, p0, r0);
+      r1 = __builtin_fma(sg, p1, r1);
+    }
+  }
+  fb[l] = dmul(r0, (double)g[l]);
+  fb[64 + l] = dmul(r1, (double)g[l + 64]);
+  wave_lds_sync();
+  double s = 0.0;
+  if (l < 4)
+    for (int e = 0; e < 32; ++e) s = dadd(s, fb[32 * l + e]);
+  const double s0 = readlane_f64(s, 0), s1 = readlane_f64(s, 1), s2 = readlane_f64(s, 2), s3 = readlane_f64(s, 3);
+  wave_lds_sync();  // fb is rewritten by the next call only after these reads
+  return dadd(dadd(s0, s1), dadd(s2, s3));
+}
+
+// ---------------------------------------------------------------------------
+// One bit: sign and bit plane of every key, and per workgroup
+// sum_j u_j k_j (fp64) and the popcounts against the earlier bit planes.
+// Bound by the read of the keys; per 64 keys a wavefront issues about 460
+// vector instructions, 384 of them the fp64 sum (widen, convert, fused add).
+// ---------------------------------------------------------------------------
+template <int W>
+__global__ __launch_bounds__(kScanThreads, 2) void build_sign_kernel(
+    const uint16_t* __restrict__ K, int64_t sK_b, int64_t sK_h, int64_t sK_n, int Hkv, int N, int bit,
+    int blocks_per_wg, int nblk, const float* __restrict__ G, const float* __restrict__ P,
+    const uint16_t* __restrict__ knorm, const float* __restrict__ tab, const double* __restrict__ corr, const float4* __restrict__ bound,
+    uint64_t* __restrict__ planes, double* __restrict__ psum, uint32_t* __restrict__ pcnt,
+    unsigned long long* __restrict__ fragile) {
+  constexpr int L = 32 * W;
+  constexpr int NP = W == 4 ? 2 : 1;  // bit planes per lane
+  __shared__ __align__(16) float tab_s[4 * W][256];
+  __shared__ double red[4][kHeadDim];
+  __shared__ uint32_t cnt_s[4][L];
+  __shared__ uint4 ga_s[4][64];
+  __shared__ int frag;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int c16 = lane & 15, g4 = lane >> 4;
+  const int bh = blockIdx.y, b = bh / Hkv, h = bh % Hkv;
+  const uint16_t* Kb = K + b * sK_b + h * sK_h;
+  const uint32_t row_bytes = (uint32_t)sK_n * 2u;
+  const float* Pb = P + (size_t)bh * L * kHeadDim;
+  const float* g = G + (size_t)bit * kHeadDim;
+  const double* cb = corr + (size_t)bh * L;
+  const int nbytes = (bit + 7) >> 3;  // code bytes that hold earlier bits
+  const int blk_begin = blockIdx.x * blocks_per_wg + wave;
+  const int blk_end = min((int)(blockIdx.x + 1) * blocks_per_wg, nblk);
+  if (tid == 0) frag = 0;
+  {
+    const float4* src = reinterpret_cast<const float4*>(tab + (size_t)bh * (4 * W) * 256);
+    for (int e = tid; e < nbytes * 64; e += kScanThreads) reinterpret_cast<float4*>(&tab_s[0][0])[e] = src[e];
+  }
+  // A operand: row c16 holds part c16 % 4 of g (hi, mid, lo, nothing), so that
+  // every lane group g4 finds its key's three products in its own D rows
+  {
+    const int m = wave;
+    const float4* gp = reinterpret_cast<const float4*>(g + 32 * m + 8 * g4);
+    uint4 hi, mid, lo;
+    split3(gp[0], gp[1], hi, mid, lo);
+    const int part = c16 & 3;
+    ga_s[m][lane] = part == 0 ? hi : part == 1 ? mid : part == 2 ? lo : make_uint4(0u, 0u, 0u, 0u);
+  }
+  const float4 bd = bound[bh];  // alpha1, beta1, alpha2, beta2
+  __syncthreads();
+
+  double acc[32];
+#pragma unroll
+  for (int e = 0; e < 32; ++e) acc[e] = 0.0;
+  uint32_t cnt[NP];
+#pragma unroll
+  for (int x = 0; x < NP; ++x) cnt[x] = 0u;
+  int nfrag = 0;
+  double* fb = red[wave];
+  for (int blk = blk_begin; blk < blk_end; blk += 4) {
+    const int base = blk * 64;
+    const bool valid = base + lane < N;
+    const float nk = bf16_to_f32(knorm[(size_t)bh * N + min(base + lane, N - 1)]);
+    // lane t: column t (and t + 64) of the 64 keys' code bits; transposed, lane
+    // j: the code words of key j so far
+    uint64_t* pl = planes + ((size_t)bh * nblk + blk) * L;
+    uint64_t col[NP];
+    uint32_t cw[2 * NP];
+#pragma unroll
+    for (int x = 0; x < NP; ++x) {
+      col[x] = lane + 64 * x < bit ? pl[lane + 64 * x] : 0ull;
+    }
+    uint4 kv[4][4];
+    load_tile(Kb, row_bytes, base, N, c16, g4, kv);
+#pragma unroll
+    for (int x = 0; x < NP; ++x) {
+      cw[2 * x] = (uint32_t)col[x], cw[2 * x + 1] = (uint32_t)(col[x] >> 32);
+      if (bit > 64 * x) transpose64(cw[2 * x], cw[2 * x + 1]);
+    }
+
+    float y = 0.f;
+    {
+      f32x4_t d[4];
+#pragma unroll
+      for (int tau = 0; tau < 4; ++tau) d[tau] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {
+        const uint4 ga = ga_s[m][lane];
+#pragma unroll
+        for (int tau = 0; tau < 4; ++tau) d[tau] = mfma32(ga, kv[tau][m], d[tau]);
+      }
+#pragma unroll
+      for (int tau = 0; tau < 4; ++tau) {
+        const float s = d[tau][0] + (d[tau][1] + d[tau][2]);
+        y = g4 == tau ? s : y;
+      }
+    }
+    // lane l from here on: key base + l
+#pragma unroll
+    for (int w = 0; w < W; ++w)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (4 * w + q < nbytes) y -= tab_s[4 * w + q][(cw[w] >> (8 * q)) & 0xFFu];
+    const float t1 = fmaf(nk, bd.x, bd.y);
+    const bool sure = !valid || (fabsf(y) > t1 && t1 < 1e30f);
+    bool u = y >= 0.f;
+    unsigned long long todo = __ballot(!sure);
+    while (todo) {
+      const int j = __ffsll((long long)todo) - 1;
+      todo &= todo - 1;
+      const uint16_t* krow = Kb + (int64_t)(base + j) * sK_n;
+      uint32_t cj[W];
+#pragma unroll
+      for (int w = 0; w < W; ++w) cj[w] = __builtin_amdgcn_readlane(cw[w], j);
+      const double nj = (double)__uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(nk), j));
+      const uint32_t kk = reinterpret_cast<const uint32_t*>(krow)[lane];
+      const float2 gg = reinterpret_cast<const float2*>(g)[lane];
+      double a = __builtin_fma(bf16_to_f64((uint16_t)(kk >> 16)), (double)gg.y,
+                               bf16_to_f64((uint16_t)(kk & 0xFFFFu)) * (double)gg.x);
+#pragma unroll
+      for (int x = 0; x < NP; ++x) {
+        const int t = lane + 64 * x;
+        uint32_t wd = cj[0];
+#pragma unroll
+        for (int w = 1; w < W; ++w) wd = (t >> 5) == w ? cj[w] : wd;
+        if (t < bit) a += ((wd >> (t & 31)) & 1u) ? -cb[t] : cb[t];
+      }
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) a += __shfl_xor(a, o, 64);
+      const double t2 = __builtin_fma(nj, (double)bd.z, (double)bd.w);
+      if (!(fabs(a) > t2 && t2 < 1e290)) {
+        a = reference_decision<W>(krow, Pb, g, bit, cj, fb);
+        if (lane == j) nfrag += fragile_decision(a) ? 1 : 0;
+      }
+      if (lane == j) u = a >= 0.0;
+    }
+    const unsigned long long M = __ballot(valid && u);
+    if (lane == 0) pl[bit] = M;
+#pragma unroll
+    for (int x = 0; x < NP; ++x)
+      if (lane + 64 * x <= bit) cnt[x] += __popcll(col[x] ^ M);  // lane `bit`: the keys with u = +1
+#pragma unroll
+    for (int tau = 0; tau < 4; ++tau) {
+      const uint32_t half = (uint32_t)(M >> (32 * (tau >> 1)));
+      const uint32_t on = (half >> (16 * (tau & 1) + c16)) & 1u;
+      const double sg = __hiloint2double((int)(0xBFF00000u ^ (on << 31)), 0);
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {
+        const uint32_t wd[4] = {kv[tau][m].x, kv[tau][m].y, kv[tau][m].z, kv[tau][m].w};
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const float f = __uint_as_float((e & 1) ? (wd[e >> 1] & 0xFFFF0000u) : (wd[e >> 1] << 16));
+          acc[8 * m + e] = __builtin_fma(sg, (double)f, acc[8 * m + e]);
+        }
+      }
+    }
+  }
+  row_reduce(acc, lane);
+  const int e0 = row_reduce_index(lane);
+#pragma unroll
+  for (int x = 0; x < 2; ++x) red[wave][32 * (e0 >> 3) + 8 * g4 + (e0 & 7) + x] = acc[x];
+#pragma unroll
+  for (int x = 0; x < NP; ++x)
+    if (lane + 64 * x < L) cnt_s[wave][lane + 64 * x] = cnt[x];
+  if (fragile && nfrag) atomicAdd(&frag, nfrag);
+  __syncthreads();
+  const size_t wg = (size_t)bh * gridDim.x + blockIdx.x;
+  if (tid < kHeadDim) psum[wg * kHeadDim + tid] = (red[0][tid] + red[1][tid]) + (red[2][tid] + red[3][tid]);
+  if (tid <= bit) pcnt[wg * L + tid] = (cnt_s[0][tid] + cnt_s[1][tid]) + (cnt_s[2][tid] + cnt_s[3][tid]);
+  if (fragile && tid == 0 && frag) atomicAdd(fragile, (unsigned long long)frag);
+}
+
+// ---------------------------------------------------------------------------
+// a + b = s + e exactly
+__device__ __forceinline__ void two_sum(double a, double b, double& s, double& e) {
+  s = a + b;
+  const double bb = s - a;
+  e = (a - (s - bb)) + (b - bb);
+}
+
+// The pairwise tree (adjacent pairs; +0 past N inside a chunk of 128 rows, the
+// odd chunk carried above) of u_j R_jd for one coordinate, in the reference
+// arithmetic, by the whole workgroup.  planes: the (b, h)'s bit planes, bits
+// 0 .. bit of 64 keys at a stride of L words; pcol: P[t][d] for t < bit; node: global
+// scratch of two doubles per chunk.
+template <int W, int NTH>
+__device__ double reference_column(const uint16_t* Kd, int64_t sK_n, const uint64_t* planes, int N, int bit,
+                                   const double* pcol, double* node) {
+  const int nch = (N + kBuildChunk - 1) / kBuildChunk;
+  for (int c = threadIdx.x; c < nch; c += NTH) {
+    double s0 = 0.0, s1 = 0.0, s2 = 0.0, root = 0.0;
+    for (int q = 0; q < kBuildChunk / 8; ++q) {
+      // eight rows at a time (one byte of each bit plane), eight independent chains
+      const int j0 = c * kBuildChunk + 8 * q;
+      double v[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] = bf16_to_f64(Kd[(int64_t)min(j0 + e, N - 1) * sK_n]);
+      const uint8_t* pb = reinterpret_cast<const uint8_t*>(planes + (size_t)(min(j0, N - 1) >> 6) * (32 * W)) + (q & 7);
+#pragma unroll 8
+      for (int t = 0; t < bit; ++t) {
+        const uint32_t s = pb[8 * t];
+        const double p = pcol[t];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = __builtin_fma(((s >> e) & 1u) ? -1.0 : 1.0, p, v[e]);
+      }
+      const uint32_t su = pb[8 * bit];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] = j0 + e >= N ? 0.0 : ((su >> e) & 1u) ? v[e] : -v[e];
+      double y = ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
+      // the 16 groups of eight of a chunk as a binary counter
+      if (q & 1) {
+        y = s0 + y;
+        if (q & 2) {
+          y = s1 + y;
+          if (q & 4) {
+            y = s2 + y;
+            if (q & 8) root = root + y;
+            else root = y;
+          } else s2 = y;
+        } else s1 = y;
+      } else s0 = y;
+    }
+    node[c] = root;
+  }
+  double* src = node;
+  double* dst = node + nch;
+  int cnt = nch;
+  while (cnt > 1) {
+    __syncthreads();
+    const int half = (cnt + 1) >> 1;
+    for (int i = threadIdx.x; i < half; i += NTH) dst[i] = 2 * i + 1 < cnt ? src[2 * i] + src[2 * i + 1] : src[2 * i];
+    double* x = src;
+    src = dst, dst = x, cnt = half;
+  }
+  __syncthreads();
+  const double r = src[0];
+  __syncthreads();
+  return r;
+}
+
+constexpr int kSolveThreads = 512;
+constexpr int kSolveSlices = kSolveThreads / kHeadDim;  // threads per coordinate
+
+// One workgroup per (b, h): P[bit] from the pass's sums, certified or summed
+// again in the reference order, then what the next pass needs: the
+// corrections c_t = P_t . g (fp64, and fp32 tables per code byte) and the
+// bounds.  With bit < 0 the first call of a build: the key statistics.
+//
+// |s - reference| <= 2^-53 1.02 (sum_x sqrt(N E_x) [the roundings of the
+// residual's subtraction x = 1 .. bit] + levels sqrt(N E) [of the tree] + chain
+// sqrt(N E_0) [of this side's sum of keys]) + 2^-51 |s|; the energies carry
+// 2^-36 E_0 of slack for their own roundings.  Most of these sums are exact and
+// then count nothing: the keys and the P[t][d] removed from them are multiples
+// of a common power of two q (of their smallest ulp), every residual is below
+// M = max |k| + sum_t |P_td|, and an addition whose result is a multiple of q
+// below 2^53 q does not round.  So the residual is exact while M < 2^53 q, the
+// tree up to the level l with 2^l M < 2^53 q, and the sum of keys when
+// N max |k| < 2^53 q.
+template <int W>
+__global__ __launch_bounds__(kSolveThreads) void build_solve_kernel(
+    const uint16_t* __restrict__ K, int64_t sK_b, int64_t sK_h, int64_t sK_n, int Hkv, int N, int bit, int nwg,
+    int chain, const float* __restrict__ G, const uint64_t* __restrict__ planes,
+    const double* __restrict__ psum, const uint32_t* __restrict__ pcnt, const uint32_t* __restrict__ pext,
+    double* __restrict__ node, float* __restrict__ P, double* __restrict__ P64, double* __restrict__ stat, double* __restrict__ cmat,
+    double* __restrict__ corr, float* __restrict__ tab, float4* __restrict__ bound) {
+  constexpr int L = 32 * W;
+  constexpr int NS = kSolveSlices;
+  constexpr int NX = (8 * L + kSolveThreads - 1) / kSolveThreads;  // rounds of eight lanes per later bit
+  __shared__ double sh[NS][kHeadDim], sl[NS][kHeadDim];
+  __shared__ double p_s[kHeadDim], a_s[kHeadDim], col_s[L], c_s[L];
+  __shared__ int n_s[L];
+  __shared__ int redo[kHeadDim], nredo;
+  const int tid = threadIdx.x, d = tid & (kHeadDim - 1), sl8 = tid >> 7;
+  const int bh = blockIdx.x, b = bh / Hkv, h = bh % Hkv;
+  // per coordinate: energies of the keys and of the residual, its sum of
+  // roundings, the chain coefficient, sum_t |P_td|, max |k| and the quantum q
+  double* E0 = stat + (size_t)bh * kScanStats * kHeadDim;
+  double* E = E0 + kHeadDim;
+  double* Rs = E + kHeadDim;
+  double* ch = Rs + kHeadDim;
+  double* Aa = ch + kHeadDim;
+  double* Kx = Aa + kHeadDim;
+  double* Qu = Kx + kHeadDim;
+  const double dN = (double)N;
+  // Every load this call will need is issued here: what follows is a chain of
+  // short steps between barriers, bound by their latency.
+  const int next = bit + 1;
+  const int part = tid & 7;
+  double pv[L / NS];
+#pragma unroll
+  for (int x = 0; x < L / NS; ++x)
+    pv[x] = sl8 + NS * x < bit ? P64[((size_t)bh * L + sl8 + NS * x) * kHeadDim + d] : 0.0;
+  double v_e0 = 0.0, v_e = 0.0, v_rs = 0.0, v_ch = 0.0, v_aa = 0.0, v_kx = 0.0, v_qu = 0.0;
+  if (bit >= 0 && tid < kHeadDim)
+    v_e0 = E0[d], v_e = E[d], v_rs = Rs[d], v_ch = ch[d], v_aa = Aa[d], v_kx = Kx[d], v_qu = Qu[d];
+  float4 gs[NX][4];
+#pragma unroll
+  for (int r = 0; r < NX; ++r) {
+    const int sx = min((tid >> 3) + r * (kSolveThreads / 8), L - 1);
+#pragma unroll
+    for (int x = 0; x < 4; ++x) gs[r][x] = reinterpret_cast<const float4*>(G + (size_t)sx * kHeadDim + 16 * part)[x];
+  }
+  const double c_old = tid < bit && next < L ? cmat[((size_t)bh * L + next) * L + tid] : 0.0;
+  float g0 = 0.f, g1 = 0.f;
+  if (tid < 64 && next < L) g0 = G[(size_t)next * kHeadDim + tid], g1 = G[(size_t)next * kHeadDim + 64 + tid];
+  // the pass's sums of keys (thread (sl8, d)) and its popcounts against the
+  // earlier bit planes (thread (sl8, t)), eight workgroups' worth per round
+  double s = 0.0;
+  int cn = 0;
+  for (int w0 = sl8; w0 < nwg; w0 += 8 * NS) {
+    double x[8];
+    int c[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const size_t w = (size_t)bh * nwg + min(w0 + NS * e, nwg - 1);
+      x[e] = psum[w * kHeadDim + d];
+      c[e] = (int)pcnt[w * L + min(d, L - 1)];
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+      if (w0 + NS * e >= nwg) x[e] = 0.0, c[e] = 0;
+    s += ((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + (x[6] + x[7]));
+    cn += ((c[0] + c[1]) + (c[2] + c[3])) + ((c[4] + c[5]) + (c[6] + c[7]));
+  }
+  if (tid < L) n_s[tid] = 0;
+  if (tid == 0) nredo = 0;
+  __syncthreads();
+  if (d <= bit) atomicAdd(&n_s[d], cn);
+
+  if (bit < 0) {
+    uint32_t mx = 0u, mn = 0x7FFFu, nz = 0u;
+    for (int w = sl8; w < nwg; w += NS) {
+      const uint32_t x = pext[((size_t)bh * nwg + w) * kHeadDim + d];
+      mx = max(mx, x & 0x7FFFu), mn = min(mn, x >> 16), nz |= x & 0x8000u;
+    }
+    sh[sl8][d] = s;
+    sl[sl8][d] = __longlong_as_double((long long)(((uint64_t)(nz | mx) << 32) | mn));
+    __syncthreads();
+    if (tid < kHeadDim) {
+      double e = 0.0;
+      mx = 0u, mn = 0x7FFFu, nz = 0u;
+#pragma unroll
+      for (int x = 0; x < NS; ++x) {
+        e += sh[x][d];
+        const uint64_t w = (uint64_t)__double_as_longlong(sl[x][d]);
+        mx = max(mx, (uint32_t)(w >> 32) & 0x7FFFu), mn = min(mn, (uint32_t)w), nz |= (uint32_t)(w >> 32) & 0x8000u;
+      }
+      // the keys' common quantum: 2^-7 of the smallest magnitude's power of
+      // two (2^-133 for denormals); every sum of them is a multiple of it
+      const double quantum = ldexp(1.0, max((int)(mn >> 7), 1) - 127 - 7);
+      const bool exact = dN * bf16_to_f64((uint16_t)mx) < 0x1p53 * quantum;
+      e *= 1.0 + 0x1p-34;
+      E0[d] = e;
+      E[d] = e;
+      Rs[d] = 0.0;
+      // an all-zero column with a negative zero in it: its sums' zero signs
+      // follow the reference order only (NaN never certifies)
+      ch[d] = (mx == 0u && nz) ? __builtin_nan("") : exact ? 0.0 : (double)chain;
+      Aa[d] = 0.0;
+      Kx[d] = bf16_to_f64((uint16_t)mx);
+      Qu[d] = quantum;
+      a_s[d] = 0.0;
+    }
+    __syncthreads();
+  } else {
+    __syncthreads();
+    // sum_t n_t P_td, each product and sum with its rounding error kept
+    double hi = 0.0, lo = 0.0;
+#pragma unroll
+    for (int x = 0; x < L / NS; ++x) {
+      if (sl8 + NS * x >= bit) break;
+      const double n = dN - 2.0 * (double)n_s[sl8 + NS * x];
+      const double p = pv[x];
+      const double q = n * p, qe = __builtin_fma(n, p, -q);
+      double e;
+      two_sum(hi, q, hi, e);
+      lo += e + qe;
+    }
+    double e;
+    two_sum(s, -hi, sh[sl8][d], e);
+    sl[sl8][d] = e - lo;
+    __syncthreads();
+    double S = 0.0, lo2 = 0.0;
+    if (tid < kHeadDim) {
+#pragma unroll
+      for (int x = 0; x < NS; ++x) {
+        two_sum(S, sh[x][d], S, e);
+        lo2 += e + sl[x][d];
+      }
+      S += lo2;
+      const double NE = sqrt(dN * (v_e + 0x1p-36 * v_e0));
+      // levels of the tree (one spare) above those whose sums are exact
+      const double M = (v_kx + v_aa) * (1.0 + 0x1p-20), top = 0x1p53 * v_qu;
+      int levels = 34 - __clz(N);
+      for (double x = M; levels > 0 && 2.0 * x < top; x *= 2.0) --levels;
+      const double B = kEps * 1.02 * (v_rs + levels * NE + v_ch * sqrt(dN * v_e0)) + 0x1p-51 * fabs(S);
+      const float pl = (float)((S - B) / dN), ph = (float)((S + B) / dN);
+      p_s[d] = (double)pl;
+      if (!(__float_as_uint(pl) == __float_as_uint(ph) && fabsf(pl) < 3e38f)) redo[atomicAdd(&nredo, 1)] = d;
+      // an all-zero column sums to +0 unless every term is -0: no key with
+      // u = +1, and no padding in the last chunk
+      else if (v_e0 == 0.0 && n_s[bit] == 0 && N % kBuildChunk == 0) p_s[d] = -0.0;
+    }
+    __syncthreads();
+    const int nr = nredo;
+    const int nblk = (N + 63) / 64;
+    for (int r = 0; r < nr; ++r) {
+      const int dd = redo[r];
+      if (tid < bit) col_s[tid] = P64[((size_t)bh * L + tid) * kHeadDim + dd];
+      __syncthreads();
+      const double T = reference_column<W, kSolveThreads>(K + b * sK_b + h * sK_h + dd, sK_n,
+                                                         planes + (size_t)bh * nblk * L, N, bit, col_s,
+                                                         node + (size_t)bh * 2 * ((N + kBuildChunk - 1) / kBuildChunk));
+      if (tid == 0) p_s[dd] = (double)(float)(T / dN);
+    }
+    __syncthreads();
+    if (tid < kHeadDim) {
+      const double p = p_s[d];
+      P[((size_t)bh * L + bit) * kHeadDim + d] = (float)p;
+      P64[((size_t)bh * L + bit) * kHeadDim + d] = p;
+      double En = v_e - 2.0 * p * S + dN * p * p;
+      En = En < 0.0 ? 0.0 : En;
+      E[d] = En;
+      const double A = v_aa + fabs(p);
+      Aa[d] = A;
+      // p is a multiple of its fp32 ulp
+      const uint32_t pe = (__float_as_uint((float)p) >> 23) & 0xFFu;
+      const double q = p == 0.0 ? v_qu : fmin(v_qu, ldexp(1.0, max((int)pe, 1) - 127 - 23));
+      Qu[d] = q;
+      if (!((v_kx + A) * (1.0 + 0x1p-20) < 0x1p53 * q)) Rs[d] = v_rs + sqrt(dN * (En + 0x1p-36 * v_e0));
+      a_s[d] = A;
+    }
+    __syncthreads();
+    // c[s][bit] = P[bit] . g_s for the bits s to come: eight lanes per s
+#pragma unroll
+    for (int r = 0; r < NX; ++r) {
+      const int sx = (tid >> 3) + r * (kSolveThreads / 8);
+      if (sx <= bit || sx >= L) continue;
+      double c = 0.0;
+#pragma unroll
+      for (int x = 0; x < 4; ++x) {
+        const double* pp = p_s + 16 * part + 4 * x;
+        c = __builtin_fma(pp[0], (double)gs[r][x].x, c);
+        c = __builtin_fma(pp[1], (double)gs[r][x].y, c);
+        c = __builtin_fma(pp[2], (double)gs[r][x].z, c);
+        c = __builtin_fma(pp[3], (double)gs[r][x].w, c);
+      }
+      c += __shfl_xor(c, 1, 64);
+      c += __shfl_xor(c, 2, 64);
+      c += __shfl_xor(c, 4, 64);
+      if (part == 0) {
+        cmat[((size_t)bh * L + sx) * L + bit] = c;
+        if (sx == next) c_s[bit] = c;
+      }
+    }
+  }
+  if (next >= L) return;
+  if (tid < L && tid != bit) c_s[tid] = c_old;
+  __syncthreads();
+  if (tid < next) corr[(size_t)bh * L + tid] = c_s[tid];
+  const int nbytes = (next + 7) >> 3;
+  for (int e = tid; e < nbytes * 256; e += kSolveThreads) {
+    const int q = e >> 8;
+    double v = 0.0;
+#pragma unroll
+    for (int x = 0; x < 8; ++x) v += ((e >> x) & 1) ? c_s[8 * q + x] : -c_s[8 * q + x];
+    tab[(size_t)bh * (4 * W) * 256 + e] = (float)v;
+  }
+  // |g|, sum_t |c_t| and Q = sum_d (sum_t |P_td|) |g_d| of the next bit
+  if (tid < 64) {
+    double n2 = (double)g0 * g0 + (double)g1 * g1, c = 0.0;
+    double q = a_s[tid] * fabs((double)g0) + a_s[tid + 64] * fabs((double)g1);
+    for (int t = tid; t < next; t += 64) c += fabs(c_s[t]);
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) n2 += __shfl_xor(n2, o, 64), q += __shfl_xor(q, o, 64), c += __shfl_xor(c, o, 64);
+    if (tid == 0) {
+      // Tier 2: the reference's (36 + i) and this side's (at most 130 + 130 +
+      // 140) roundings of sums below |k| |g| + Q, and the fragile threshold.
+      // Tier 1: the matrix-core chains (138 u |k| |g|), up to 19 fp32 additions
+      // of table entries (u (|k| |g| + C) each), u = 2^-24; underflow of bf16
+      // parts, products and keys.
+      const double gl = sqrt(n2) * (1.0 + 0x1p-20) + 0x1p-500;
+      const double a2 = 0x1p-43 * gl, b2 = 0x1p-43 * q + 1.01e-6;
+      const double a1 = 160.0 * 0x1p-24 * gl + 0x1p-100 + a2;
+      const double b1 = 24.0 * 0x1p-24 * c + b2 + 0x1p-109 * (1.0 + gl);
+      const double up = 1.0 + 0x1p-8;
+      bound[bh] = make_float4((float)(a1 * up), (float)(b1 * up), (float)(a2 * up), (float)(b2 * up));
+    }
+  }
+}
+
+// The code words of every key from the bit planes: one wavefront per 64 keys.
+template <int W>
+__global__ __launch_bounds__(kScanThreads) void build_codes_kernel(const uint64_t* __restrict__ planes, int Hkv, int N,
+                                                                   int nblk, uint32_t* __restrict__ codes,
+                                                                   int64_t sC_b, int64_t sC_h) {
+  constexpr int L = 32 * W;
+  constexpr int NP = W == 4 ? 2 : 1;
+  const int lane = threadIdx.x & 63, blk = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int bh = blockIdx.y, b = bh / Hkv, h = bh % Hkv;
+  if (blk >= nblk) return;
+  const uint64_t* pl = planes + ((size_t)bh * nblk + blk) * L;
+  uint32_t cw[2 * NP];
+#pragma unroll
+  for (int x = 0; x < NP; ++x) {
+    const uint64_t col = lane + 64 * x < L ? pl[lane + 64 * x] : 0ull;
+    cw[2 * x] = (uint32_t)col, cw[2 * x + 1] = (uint32_t)(col >> 32);
+    transpose64(cw[2 * x], cw[2 * x + 1]);
+  }
+  const int key = blk * 64 + lane;
+  if (key >= N) return;
+  uint32_t* cp = codes + b * sC_b + h * sC_h + (int64_t)key * W;
+  if constexpr (W == 1) cp[0] = cw[0];
+  else if constexpr (W == 2) *reinterpret_cast<uint2*>(cp) = make_uint2(cw[0], cw[1]);
+  else *reinterpret_cast<uint4*>(cp) = make_uint4(cw[0], cw[1], cw[2], cw[3]);
+}
+
+template <int W>
+static void launch_build_scan_W(const BuildArgs& a, const BuildLayout& lay) {
+  constexpr int L = 32 * W;
+  const int BH = a.B * a.Hkv;
+  char* ws = a.ws;
+  double* psum = reinterpret_cast<double*>(ws + lay.off_psum);
+  uint32_t* pcnt = reinterpret_cast<uint32_t*>(ws + lay.off_pcnt);
+  uint64_t* planes = reinterpret_cast<uint64_t*>(ws + lay.off_planes);
+  uint16_t* knorm = reinterpret_cast<uint16_t*>(ws + lay.off_knorm);
+  double* node = reinterpret_cast<double*>(ws + lay.off_node);
+  double* P64 = reinterpret_cast<double*>(ws + lay.off_p64);
+  double* stat = reinterpret_cast<double*>(ws + lay.off_stat);
+  double* cmat = reinterpret_cast<double*>(ws + lay.off_cmat);
+  double* corr = reinterpret_cast<double*>(ws + lay.off_corr);
+  float* tab = reinterpret_cast<float*>(ws + lay.off_tab);
+  float4* bound = reinterpret_cast<float4*>(ws + lay.off_bound);
+  const dim3 grid(lay.scan_wgs, BH);
+  const int bpw = lay.scan_blocks, nblk = (a.N + 63) / 64;
+  // additions one key passes through on this side: a lane's own chain, the
+  // row, wavefront and workgroup levels
+  const int chain = bpw + lay.scan_wgs / 4 + 32;
+  build_stat_kernel<<<grid, kScanThreads, 0, a.stream>>>(a.K, a.sK_b, a.sK_h, a.sK_n, a.Hkv, a.N, bpw, psum, pcnt,
+                                                         knorm, nblk);
+  for (int bit = -1; bit < L; ++bit) {
+    if (bit >= 0)
+      build_sign_kernel<W><<<grid, kScanThreads, 0, a.stream>>>(a.K, a.sK_b, a.sK_h, a.sK_n, a.Hkv, a.N, bit, bpw,
+                                                                nblk, a.G, a.P, knorm, tab, corr, bound, planes, psum, pcnt, a.fragile);
+    build_solve_kernel<W><<<BH, kSolveThreads, 0, a.stream>>>(a.K, a.sK_b, a.sK_h, a.sK_n, a.Hkv, a.N, bit,
+                                                              lay.scan_wgs, chain, a.G, planes, psum, pcnt, pcnt, node, a.P, P64, stat, cmat, corr, tab,
+                                                              bound);
+  }
+  build_codes_kernel<W><<<dim3((nblk + 3) / 4, BH), kScanThreads, 0, a.stream>>>(planes, a.Hkv, a.N, nblk, a.codes,
+                                                                                 a.sC_b, a.sC_h);
+}
+
+void launch_build_scan(const BuildArgs& a, const BuildLayout& lay) {
+  switch (a.L) {
+    case 32: launch_build_scan_W<1>(a, lay); break;
+    case 64: launch_build_scan_W<2>(a, lay); break;
+    default: launch_build_scan_W<4>(a, lay); break;
+  }
+}
+
+}  // namespace bpc

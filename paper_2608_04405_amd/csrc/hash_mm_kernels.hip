@@ -47,11 +47,9 @@
 // Non-finite values make every comparison fail and take the same route.
 
 #include "bpc_internal.h"
+#include "mfma_split.h"
 
 namespace bpc {
-
-typedef short bf16x8_t __attribute__((ext_vector_type(8)));
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 // 64 keys per wavefront per iteration; four wavefronts per workgroup, eight
 // at L = 128, where one workgroup fills a CU's LDS
@@ -59,54 +57,6 @@ template <int L>
 constexpr int hm_threads() { return L == 128 ? 512 : 256; }
 constexpr int kHmPsStride = 132;     // fp32 P row stride in LDS (floats)
 constexpr int kHmXsStride = 20;      // transpose buffer row stride (floats)
-
-// D += A B for one 16 x 16 x 32 bf16 tile (fp32 accumulation).  Lane i
-// supplies A[i % 16][8 (i / 16) + j] and B[8 (i / 16) + j][i % 16] for
-// j = 0..7 (two bf16 per word, low half first) and holds D[4 (i / 16) + j]
-// [i % 16] for j = 0..3.  The order of the coordinates inside a lane only has
-// to agree between A and B.
-__device__ __forceinline__ f32x4_t mfma32(const uint4 a, const uint4 b, f32x4_t d) {
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b),
-                                                 d, 0, 0, 0);
-}
-
-// Eight fp32 values cut exactly into three bf16 parts: hi keeps the top 8
-// significant bits, mid the next 8, lo the rest (at most 8 significant bits
-// remain once hi and mid are subtracted; both subtractions are exact).
-__device__ __forceinline__ void split3(const float4 p0, const float4 p1, uint4& hi, uint4& mid, uint4& lo) {
-  const float v[8] = {p0.x, p0.y, p0.z, p0.w, p1.x, p1.y, p1.z, p1.w};
-  uint32_t h[8], m[8], l[8];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const uint32_t bh = __float_as_uint(v[e]) & 0xFFFF0000u;
-    const float r1 = v[e] - __uint_as_float(bh);
-    const uint32_t bm = __float_as_uint(r1) & 0xFFFF0000u;
-    const float r2 = r1 - __uint_as_float(bm);
-    h[e] = bh, m[e] = bm, l[e] = __float_as_uint(r2);
-  }
-  hi = make_uint4(__builtin_amdgcn_perm(h[1], h[0], 0x07060302u), __builtin_amdgcn_perm(h[3], h[2], 0x07060302u),
-                  __builtin_amdgcn_perm(h[5], h[4], 0x07060302u), __builtin_amdgcn_perm(h[7], h[6], 0x07060302u));
-  mid = make_uint4(__builtin_amdgcn_perm(m[1], m[0], 0x07060302u), __builtin_amdgcn_perm(m[3], m[2], 0x07060302u),
-                   __builtin_amdgcn_perm(m[5], m[4], 0x07060302u), __builtin_amdgcn_perm(m[7], m[6], 0x07060302u));
-  lo = make_uint4(__builtin_amdgcn_perm(l[1], l[0], 0x07060302u), __builtin_amdgcn_perm(l[3], l[2], 0x07060302u),
-                  __builtin_amdgcn_perm(l[5], l[4], 0x07060302u), __builtin_amdgcn_perm(l[7], l[6], 0x07060302u));
-}
-
-__device__ __forceinline__ void wave_lds_sync() {
-  // LDS operations of one wavefront complete in order; the fences keep the
-  // compiler from moving LDS accesses across this point
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-__device__ __forceinline__ double readlane_f64(double x, int lane) {
-  const uint64_t b = __double_as_longlong(x);
-  const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)b, lane);
-  const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(b >> 32), lane);
-  return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
-}
-
 
 // Decision `bit` of one key in the reference arithmetic, computed by the
 // whole wavefront: lane l carries coordinates l and l + 64 of the residual,

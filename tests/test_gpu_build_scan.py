@@ -1,0 +1,136 @@
+"""The scanning build of Algorithm 1 (closed-form sums, certified signs and
+certified rows of P) against the build that rebuilds every residual in the
+reference arithmetic, which runs on a workspace too small for the former: the
+same P, codes, errors and fragile counts bit for bit.  (Both are checked
+against the oracle in test_gpu_parity.py and test_gpu_fullsize.py.)"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2608_04405_amd as bpc
+from _helpers import bits_of
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+def small_workspace(B, H, N, L):
+    """The bytes the residual-rebuilding build needs: one fp64 sum per
+    128-key chunk and coordinate (and per 32 chunks when there are more than
+    256), P and G in fp64."""
+    nch = -(-N // 128)
+    nfold = -(-nch // 32) if nch > 256 else 0
+    return 1024 * (B * H * (nch + nfold + L) + L)
+
+
+def both(K, G, N, codes_stride_rows=0):
+    B, H = K.shape[:2]
+    L = G.shape[0]
+    res = []
+    sizes = [bpc.build_workspace_bytes(B, H, N, L), small_workspace(B, H, N, L)]
+    for size in sizes:
+        ws = torch.randint(0, 256, (size,), dtype=torch.uint8, device=DEV)
+        codes = torch.full((B, H, N + codes_stride_rows, L // 32), 0x5A5A5A5A, dtype=torch.int32, device=DEV)
+        err = torch.empty(B, H, N, device=DEV)
+        frag = torch.zeros(1, dtype=torch.int64, device=DEV)
+        P, codes, err = bpc.build_hash(K, G, N=N, codes_out=codes, err_out=err, fragile=frag, workspace=ws)
+        torch.cuda.synchronize()
+        assert (codes[:, :, N:] == 0x5A5A5A5A).all()
+        res.append((P, codes, err, int(frag)))
+    if sizes[1] >= sizes[0]:  # a few keys: any accepted workspace holds the scanning build
+        res[1] = by_oracle(K, G, N)
+    return res
+
+
+def by_oracle(K, G, N):
+    B, H = K.shape[:2]
+    out = [oracle.build_binary_pcs(bits_of(K)[b, h, :N], G.cpu().numpy()) for b in range(B) for h in range(H)]
+    P, codes, err = (np.stack([o[i] for o in out]) for i in range(3))
+    return (torch.from_numpy(P).reshape(B, H, -1, 128).to(DEV),
+            torch.from_numpy(codes.view(np.int32)).reshape(B, H, N, -1).to(DEV),
+            torch.from_numpy(err.astype(np.float32)).reshape(B, H, N).to(DEV), sum(int(o[3]) for o in out))
+
+
+def assert_same(res):
+    (P, c, e, f), (P2, c2, e2, f2) = res
+    c = c[:, :, :e.shape[2]]
+    c2 = c2[:, :, :e.shape[2]]
+    assert torch.equal(c, c2)
+    same = (P.view(torch.int32) == P2.view(torch.int32)) | (P.isnan() & P2.isnan())
+    assert bool(same.all()), int((~same).sum())
+    assert bool(((e == e2) | (e.isnan() & e2.isnan())).all())
+    assert f == f2
+
+
+def keys(N, B=1, H=2, seed=0, rank=8, noise=0.1):
+    g = torch.Generator(device=DEV).manual_seed(seed)
+    A = torch.randn(H, rank, 128, generator=g, device=DEV)
+    Z = torch.randn(B, H, N, rank, generator=g, device=DEV)
+    x = torch.randn(B, H, N, 128, generator=g, device=DEV) * noise
+    for r in range(rank):
+        x += Z[..., r:r + 1] * A[:, r:r + 1]
+    return x.to(torch.bfloat16)
+
+
+def directions(L, seed=1):
+    return torch.randn(L, 128, generator=torch.Generator(device=DEV).manual_seed(seed), device=DEV)
+
+
+# one key; one short, one whole, one whole and a bit 64-key tile; a 128-key
+# chunk and a bit; a wavefront's and a workgroup's share and a bit; more than
+# one block per wavefront
+@pytest.mark.parametrize("L,N,B,H", [(32, 1, 1, 1), (64, 63, 1, 2), (64, 64, 2, 1), (128, 65, 1, 2), (32, 129, 1, 3),
+                                     (64, 257, 1, 1), (128, 1025, 2, 2), (64, 40961, 1, 8)])
+def test_sizes(L, N, B, H):
+    print(f"[build scan] L={L} N={N} B={B} H={H}", flush=True)
+    assert_same(both(keys(N, B, H, seed=N), directions(L), N, codes_stride_rows=3))
+
+
+FORMS = ["zero_columns", "negative_zero_columns", "cancelling", "tiny_and_huge", "outlier_key", "denormal", "constant",
+         "zero", "infinite", "strided"]
+
+
+@pytest.mark.parametrize("L", [32, 64, 128])
+@pytest.mark.parametrize("form", FORMS)
+def test_forms(form, L):
+    N = 640 if form != "strided" else 700
+    print(f"[build scan] {form} L={L}", flush=True)
+    K = keys(N, seed=L)
+    if form == "zero_columns":  # heads of 64 padded to 128: those columns of P are zero
+        K[..., 64:] = 0
+    elif form == "negative_zero_columns":
+        K[..., 5] = 0
+        K[..., 5] = -K[..., 5]
+        K[:, :, ::2, 9] = 0
+        K[:, :, 1::2, 9] = -torch.zeros_like(K[:, :, 1::2, 9])
+    elif form == "cancelling":  # u k = the same for k and -k: residuals cancel exactly
+        K[:, :, N // 2:] = -K[:, :, :N // 2]
+    elif form == "tiny_and_huge":  # magnitudes span more than fp64 sums hold exactly
+        K[:, :, ::3] *= 2.0 ** -60
+        K[:, :, 1::7] *= 2.0 ** 20
+    elif form == "outlier_key":  # one key's norm far above the others'
+        K[:, :, 11] *= 2.0 ** 12
+    elif form == "denormal":
+        K = (K.float() * 2.0 ** -128).to(torch.bfloat16)
+    elif form == "constant":
+        K[:] = K[:, :, :1]
+    elif form == "zero":
+        K.zero_()
+    elif form == "infinite":
+        K[0, 0, 17, 3] = float("inf")
+        K[0, 1, 100, 77] = float("nan")
+    elif form == "strided":  # rows of 136 elements, heads interleaved
+        K = torch.zeros(1, N, 2, 136, dtype=torch.bfloat16, device=DEV).transpose(1, 2)[..., :128].copy_(K)
+    assert_same(both(K, directions(L), N if form != "strided" else N - 57))
+
+
+def test_many_uncertified_columns():
+    """Directions in which the residual's sum is far below its terms: P rows
+    near rounding boundaries of a coarse grid, so that columns are summed again
+    in the reference order."""
+    N, L = 2048, 64
+    g = torch.Generator(device=DEV).manual_seed(3)
+    K = torch.randint(-4, 5, (1, 2, N, 128), generator=g, device=DEV).to(torch.bfloat16)
+    K[:, :, ::2] = -K[:, :, 1::2]
+    assert_same(both(K, directions(L), N))
