@@ -173,7 +173,9 @@ int bpc_build_hash(const uint16_t* K, int64_t sK_b, int64_t sK_h, int64_t sK_n,
  * codes_out  [B, Hkv, >=N, W] uint32, strides sC_b, sC_h (written)
  * err_out    [B, Hkv, N] fp32 contiguous ||r_final|| (or NULL)
  * fragile_out  device uint64 accumulator (or NULL), as above.
- * No workspace; one kernel launch.
+ * No workspace; one kernel launch, and one more for err_out.  The codes come
+ * from the kernel of bpc_hash_keys_mm (below: certified signs, every other
+ * decision in the arithmetic above), the norms from the residual itself.
  */
 int bpc_hash_keys(const uint16_t* K, int64_t sK_b, int64_t sK_h, int64_t sK_n,
                   int B, int Hkv, int N, int D, int L,
@@ -196,9 +198,10 @@ int bpc_hash_keys(const uint16_t* K, int64_t sK_b, int64_t sK_h, int64_t sK_n,
  * every other decision is recomputed in that fixed-order arithmetic.
  *
  * Arguments as for bpc_hash_keys, without err_out (residual norms need the
- * fp64 residual itself: use bpc_hash_keys for them).
+ * fp64 residual itself: bpc_hash_keys computes them in a second launch).
  * fallbacks_out  device uint64 accumulator (or NULL): decisions recomputed
- *            in the fixed-order arithmetic.
+ *            in the fixed-order arithmetic (every decision of 64 neighbouring
+ *            keys when many of theirs are uncertain).
  * No workspace; one kernel launch.
  */
 int bpc_hash_keys_mm(const uint16_t* K, int64_t sK_b, int64_t sK_h, int64_t sK_n,

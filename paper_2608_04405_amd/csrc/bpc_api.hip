@@ -244,8 +244,11 @@ int bpc_hash_keys(const uint16_t* K, int64_t sK_b, int64_t sK_h, int64_t sK_n, i
   if ((st = check_proj(P, sP_b, sP_h))) return st;
   if ((st = check_codes("codes_out", codes_out, sC_b, sC_h, L / 32))) return st;
   if ((st = check_opt_aligned("err_out", err_out))) return st;
-  hipError_t e = launch_hash(K, sK_b, sK_h, sK_n, B, Hkv, N, L, P, sP_b, sP_h, codes_out, sC_b, sC_h, err_out,
-                             fragile_out, static_cast<hipStream_t>(stream));
+  hipError_t e = launch_hash_mm(K, sK_b, sK_h, sK_n, B, Hkv, N, L, P, sP_b, sP_h, codes_out, sC_b, sC_h, fragile_out,
+                                nullptr, static_cast<hipStream_t>(stream));
+  if (e == hipSuccess && err_out)
+    e = launch_norm(K, sK_b, sK_h, sK_n, B, Hkv, N, L, P, sP_b, sP_h, codes_out, sC_b, sC_h, err_out,
+                    static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return hip_fail(e, "bpc_hash_keys launch");
   return BPC_OK;
 }

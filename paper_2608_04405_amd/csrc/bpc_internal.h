@@ -195,6 +195,11 @@ hipError_t launch_hash_mm(const uint16_t* K, int64_t sK_b, int64_t sK_h, int64_t
                           const float* P, int64_t sP_b, int64_t sP_h, uint32_t* codes, int64_t sC_b, int64_t sC_h,
                           unsigned long long* fragile, unsigned long long* fallbacks, hipStream_t stream);
 
+// ||k - h P|| of hashed keys in the fixed-order fp64 arithmetic
+hipError_t launch_norm(const uint16_t* K, int64_t sK_b, int64_t sK_h, int64_t sK_n, int B, int Hkv, int N, int L,
+                       const float* P, int64_t sP_b, int64_t sP_h, const uint32_t* codes, int64_t sC_b, int64_t sC_h,
+                       float* err, hipStream_t stream);
+
 struct BuildArgs {
   const uint16_t* K;
   int64_t sK_b, sK_h, sK_n;

@@ -41,8 +41,7 @@ namespace bpc {
 //                       v = s / N,
 //                       P[i] = (float)v (and its fp64 widening for the next
 //                       passes).
-// A final build_bit pass (bit == L) recomputes the last residual and writes
-// ||R_j||.  Nothing of size N x D is stored: the pass reads the keys again,
+// Nothing of size N x D is stored: the pass reads the keys again,
 // trading fp64 arithmetic (about L^2 D / 2 fused subtractions per key over the
 // whole build) for memory traffic.
 // ============================================================================
@@ -95,8 +94,7 @@ template <int W>
 __global__ __launch_bounds__(kBuildThreads) void build_bit_kernel(
     const uint16_t* __restrict__ K, int64_t sK_b, int64_t sK_h, int64_t sK_n, int Hkv, int N, int L, int bit,
     const double* __restrict__ G64, const double* __restrict__ P64, uint32_t* __restrict__ codes, int64_t sC_b,
-    int64_t sC_h, double* __restrict__ part, int nchunks, float* __restrict__ err,
-    unsigned long long* __restrict__ fragile) {
+    int64_t sC_h, double* __restrict__ part, int nchunks, unsigned long long* __restrict__ fragile) {
   __shared__ double xch[kBuildGroups][4][64];         // per-block partial dots of each key
   __shared__ double groot[kBuildGroups][kHeadDim];    // tree root of each key group
   __shared__ int frag;
@@ -105,7 +103,6 @@ __global__ __launch_bounds__(kBuildThreads) void build_bit_kernel(
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c = wv & 3, grp = wv >> 2;
-  const bool final_pass = (bit == L);
   if (threadIdx.x == 0) frag = 0;
 
   const int key = blockIdx.x * kBuildChunk + grp * 64 + lane;
@@ -144,17 +141,6 @@ __global__ __launch_bounds__(kBuildThreads) void build_bit_kernel(
 #pragma unroll
       for (int e = 0; e < 32; ++e) r[e] = __builtin_fma(sg, p[e], r[e]);
     }
-  }
-  if (final_pass) {
-    double sq = 0.0;
-#pragma unroll
-    for (int e = 0; e < 32; ++e) sq = dadd(sq, dmul(r[e], r[e]));
-    xch[grp][c][lane] = sq;
-    __syncthreads();
-    if (err && c == 0 && valid)
-      err[(size_t)bh * N + key] = (float)sqrt(dadd(dadd(xch[grp][0][lane], xch[grp][1][lane]),
-                                                   dadd(xch[grp][2][lane], xch[grp][3][lane])));
-    return;
   }
   // a_j = R_j . g (four blocks of 32, ascending, combined ((b0 + b1) + (b2 + b3)))
   const_ptr<double> g = uniform_ptr(G64 + (size_t)bit * kHeadDim + 32 * c);
@@ -296,13 +282,10 @@ static void launch_build_W(const BuildArgs& a, const BuildLayout& lay, bool scan
     const int ng = a.L * kHeadDim;
     build_prep_kernel<<<(ng + 255) / 256, 256, 0, a.stream>>>(a.G, G64, ng);
   }
-  // after a scanning build only the residual norms remain
-  for (int bit = scan ? a.L : 0; bit <= a.L; ++bit) {
-    if (bit == a.L && !a.err) break;
+  for (int bit = 0; bit < a.L && !scan; ++bit) {
     build_bit_kernel<W><<<grid, kBuildThreads, 0, a.stream>>>(a.K, a.sK_b, a.sK_h, a.sK_n, a.Hkv, a.N, a.L, bit, G64,
-                                                             P64, a.codes, a.sC_b, a.sC_h, part, lay.nchunks, a.err,
+                                                             P64, a.codes, a.sC_b, a.sC_h, part, lay.nchunks,
                                                              a.fragile);
-    if (bit == a.L) break;
     if (lay.nfold) {
       build_fold_kernel<<<dim3(lay.nfold, BH), kHeadDim, 0, a.stream>>>(part, lay.nchunks, fold, lay.nfold);
       build_finish_kernel<<<BH, kFinishBlocks * kHeadDim, 0, a.stream>>>(a.N, a.L, bit, lay.nfold, fold, a.P, P64);
@@ -321,11 +304,125 @@ hipError_t launch_build(const BuildArgs& a, bool scan) {
     case 64: launch_build_W<2>(a, lay, scan); break;
     default: launch_build_W<4>(a, lay, scan); break;
   }
+  if (a.err)
+    return launch_norm(a.K, a.sK_b, a.sK_h, a.sK_n, a.B, a.Hkv, a.N, a.L, a.P, (int64_t)a.Hkv * a.L * kHeadDim,
+                       (int64_t)a.L * kHeadDim, a.codes, a.sC_b, a.sC_h, a.err, a.stream);
   return hipGetLastError();
 }
 
 // ============================================================================
-// Algorithm 2.  Four lanes per key: lane q of a quad holds the fp64
+// Residual norms ||k - h P|| of hashed keys, in the reference arithmetic: each
+// coordinate's residual by one rounded subtraction per bit (a fused one, the
+// product with u = +-1 being exact), the squares summed in four blocks of 32.
+//
+// Bound by the L x 128 fp64 subtractions per key (4 cycles each per
+// wavefront).  A wavefront owns one block of 32 coordinates of 256 keys, four
+// keys per lane, and takes it in two halves of 16 so that the 64 residuals fit
+// registers; the rows of P are staged in LDS already widened, 32 at a time, and
+// each entry read there serves four subtractions.  3.2 M keys at L = 64 (a
+// batch of 4 x 8 heads x 100003): 1.05 ms, of which the subtractions and squares
+// are 0.9 at the rate they issue; reading P as scalars and widening it in every
+// wavefront took 1.35 ms, and the kernel that decided the signs in the same
+// arithmetic 4.34.
+// ============================================================================
+constexpr int kNormKeys = 256;  // keys per workgroup: four per lane of each of four wavefronts
+
+template <int W>
+__global__ __launch_bounds__(256, 2) void norm_kernel(const uint16_t* __restrict__ K, int64_t sK_b, int64_t sK_h,
+                                                      int64_t sK_n, int Hkv, int N, const float* __restrict__ P,
+                                                      int64_t sP_b, int64_t sP_h,
+                                                      const uint32_t* __restrict__ codes, int64_t sC_b, int64_t sC_h,
+                                                      float* __restrict__ err) {
+  __shared__ double xch[4][kNormKeys];
+  __shared__ __align__(16) double ps[32][64];  // 32 rows of P, one half of every block, widened
+  const int bh = blockIdx.y, b = bh / Hkv, h = bh % Hkv;
+  const int lane = threadIdx.x & 63;
+  const int c = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint16_t* Kb = K + b * sK_b + h * sK_h + 32 * c;
+  const uint32_t* Cb = codes + b * sC_b + h * sC_h;
+  const float* Pb = P + b * sP_b + h * sP_h;
+  const int key0 = blockIdx.x * kNormKeys + lane;
+  uint32_t cw[4][W];
+#pragma unroll
+  for (int x = 0; x < 4; ++x)
+#pragma unroll
+    for (int w = 0; w < W; ++w) cw[x][w] = Cb[(int64_t)min(key0 + 64 * x, N - 1) * W + w];
+  double sq[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 1
+  for (int half = 0; half < 2; ++half) {
+    double r[4][16];
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+      const uint4* row = reinterpret_cast<const uint4*>(Kb + (int64_t)min(key0 + 64 * x, N - 1) * sK_n + 16 * half);
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const uint4 v = row[q];
+        const uint32_t wd[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          r[x][8 * q + e] = bf16_to_f64((uint16_t)((e & 1) ? (wd[e >> 1] >> 16) : (wd[e >> 1] & 0xFFFFu)));
+      }
+    }
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+      __syncthreads();
+      for (int e = threadIdx.x; e < 32 * 16; e += 256) {
+        const int t = e >> 4, q = e & 15;  // four floats: block q / 4, part q % 4 of its half
+        const float4 v = *reinterpret_cast<const float4*>(Pb + (size_t)(32 * w + t) * kHeadDim + 32 * (q >> 2) +
+                                                          16 * half + 4 * (q & 3));
+        double* o = &ps[t][4 * q];
+        o[0] = v.x, o[1] = v.y, o[2] = v.z, o[3] = v.w;
+      }
+      __syncthreads();
+#pragma unroll 2
+      for (int t = 0; t < 32; ++t) {
+        const double* p = &ps[t][16 * c];
+        double sg[4];
+#pragma unroll
+        for (int x = 0; x < 4; ++x)
+          sg[x] = __hiloint2double((int)(0x3FF00000u | ((cw[x][w] >> t) << 31)), 0);  // -u
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          const double pv = p[e];
+#pragma unroll
+          for (int x = 0; x < 4; ++x) r[x][e] = __builtin_fma(sg[x], pv, r[x][e]);
+        }
+      }
+    }
+#pragma unroll
+    for (int x = 0; x < 4; ++x)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) sq[x] = dadd(sq[x], dmul(r[x][e], r[x][e]));
+  }
+#pragma unroll
+  for (int x = 0; x < 4; ++x) xch[c][64 * x + lane] = sq[x];
+  __syncthreads();
+  const int key = blockIdx.x * kNormKeys + threadIdx.x;
+  if (key < N)
+    err[(size_t)bh * N + key] = (float)sqrt(dadd(dadd(xch[0][threadIdx.x], xch[1][threadIdx.x]),
+                                                 dadd(xch[2][threadIdx.x], xch[3][threadIdx.x])));
+}
+
+hipError_t launch_norm(const uint16_t* K, int64_t sK_b, int64_t sK_h, int64_t sK_n, int B, int Hkv, int N, int L,
+                       const float* P, int64_t sP_b, int64_t sP_h, const uint32_t* codes, int64_t sC_b, int64_t sC_h,
+                       float* err, hipStream_t stream) {
+  const dim3 grid((N + kNormKeys - 1) / kNormKeys, B * Hkv);
+  switch (L) {
+    case 32:
+      norm_kernel<1><<<grid, 256, 0, stream>>>(K, sK_b, sK_h, sK_n, Hkv, N, P, sP_b, sP_h, codes, sC_b, sC_h, err);
+      break;
+    case 64:
+      norm_kernel<2><<<grid, 256, 0, stream>>>(K, sK_b, sK_h, sK_n, Hkv, N, P, sP_b, sP_h, codes, sC_b, sC_h, err);
+      break;
+    default:
+      norm_kernel<4><<<grid, 256, 0, stream>>>(K, sK_b, sK_h, sK_n, Hkv, N, P, sP_b, sP_h, codes, sC_b, sC_h, err);
+      break;
+  }
+  return hipGetLastError();
+}
+
+// ============================================================================
+// Algorithm 2 for decode-time append.  Four lanes per key: lane q of a quad holds the fp64
 // residual of coordinates [32q, 32q + 32) in registers, so each bit's dot
 // product is four sequential block sums combined across the quad as
 // ((b0 + b1) + (b2 + b3)) -- the fixed order -- and the residual update

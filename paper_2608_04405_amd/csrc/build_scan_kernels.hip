@@ -203,6 +203,61 @@ __device__ __forceinline__ double reference_decision(const uint16_t* krow, const
   return dadd(dadd(s0, s1), dadd(s2, s3));
 }
 
+// The same decisions for all 64 keys of a tile at once, one key per lane (each
+// lane reads its own row; g, P and the corrections are the same in every lane):
+// first in fp64 without the residual, then, where `todo` asks for it, in the
+// reference arithmetic.
+template <int W>
+__device__ __forceinline__ double lane_decision(const uint16_t* row, const double* cb, const float* g, int bit,
+                                                const uint32_t* cw) {
+  double a = 0.0;
+#pragma unroll 1
+  for (int q = 0; q < kHeadDim / 8; ++q) {
+    const uint4 v = reinterpret_cast<const uint4*>(row)[q];
+    const uint32_t wd[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+      a = __builtin_fma(bf16_to_f64((uint16_t)((e & 1) ? (wd[e >> 1] >> 16) : (wd[e >> 1] & 0xFFFFu))),
+                        (double)g[8 * q + e], a);
+  }
+#pragma unroll
+  for (int w = 0; w < W; ++w)
+    for (int t = 32 * w; t < min(bit, 32 * w + 32); ++t) a += ((cw[w] >> (t & 31)) & 1u) ? -cb[t] : cb[t];
+  return a;
+}
+template <int W>
+__device__ __forceinline__ double lane_reference_decision(const uint16_t* row, const float* Pb, const float* g, int bit,
+                                                          const uint32_t* cw) {
+  double blk[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    double s = 0.0;
+#pragma unroll 1
+    for (int q = 0; q < 4; ++q) {
+      const int d0 = 32 * c + 8 * q;
+      const uint4 v = *reinterpret_cast<const uint4*>(row + d0);
+      const uint32_t wd[4] = {v.x, v.y, v.z, v.w};
+      double r[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        r[e] = bf16_to_f64((uint16_t)((e & 1) ? (wd[e >> 1] >> 16) : (wd[e >> 1] & 0xFFFFu)));
+#pragma unroll
+      for (int w = 0; w < W; ++w)
+        for (int t = 32 * w; t < min(bit, 32 * w + 32); ++t) {
+          const double sg = ((cw[w] >> (t & 31)) & 1u) ? -1.0 : 1.0;
+#pragma unroll
+          for (int e = 0; e < 8; ++e) r[e] = __builtin_fma(sg, (double)Pb[t * kHeadDim + d0 + e], r[e]);
+        }
+#pragma unroll
+      for (int e = 0; e < 8; ++e) s = dadd(s, dmul(r[e], (double)g[d0 + e]));
+    }
+    blk[c] = s;
+  }
+  return dadd(dadd(blk[0], blk[1]), dadd(blk[2], blk[3]));
+}
+// uncertain keys of a tile above which all its keys are decided at once
+constexpr int kScanMany = 16;
+
 // ---------------------------------------------------------------------------
 // One bit: sign and bit plane of every key, and per workgroup
 // sum_j u_j k_j (fp64) and the popcounts against the earlier bit planes.
@@ -309,6 +364,22 @@ __global__ __launch_bounds__(kScanThreads, 2) void build_sign_kernel(
     const bool sure = !valid || (fabsf(y) > t1 && t1 < 1e30f);
     bool u = y >= 0.f;
     unsigned long long todo = __ballot(!sure);
+    if (__popcll(todo) > kScanMany) {
+      const uint16_t* row = Kb + (int64_t)min(base + lane, N - 1) * sK_n;
+      const double a = lane_decision<W>(row, cb, g, bit, cw);
+      const double t2 = __builtin_fma((double)nk, (double)bd.z, (double)bd.w);
+      const bool sure2 = sure || (fabs(a) > t2 && t2 < 1e290);
+      if (!sure) u = a >= 0.0;
+      todo = __ballot(!sure2);
+      if (__popcll(todo) > kScanMany) {
+        const double ar = lane_reference_decision<W>(row, Pb, g, bit, cw);
+        if (!sure2) {
+          u = ar >= 0.0;
+          nfrag += fragile_decision(ar) ? 1 : 0;
+        }
+        todo = 0ull;
+      }
+    }
     while (todo) {
       const int j = __ffsll((long long)todo) - 1;
       todo &= todo - 1;

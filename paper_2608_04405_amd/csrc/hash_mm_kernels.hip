@@ -46,15 +46,36 @@
 // order, and the four-block dot; the fragile test is then the reference's.
 // Non-finite values make every comparison fail and take the same route.
 
+//
+// Where more than kHmMany of a tile's 64 keys are uncertain in one block of
+// bits (rank-deficient keys, a P that fits them exactly) the whole tile is
+// decided in the reference arithmetic, four lanes per key; rows of P that are
+// zero need neither.
+//
+// What bounds it: vector issue and LDS reads (each block's triangle of
+// corrections, its operands read uniformly from LDS), at two wavefronts per
+// SIMD.  Batch 16 x 8 heads x 131072 keys, L = 64: 2.44 ms (2.67 before the
+// parts of P were cut once per workgroup, the certificate was folded into one
+// multiply-add per bit, the next tile's keys were loaded during the last block's
+// decisions and the set-up moved to the fp64 matrix cores); 8 x 1048576 keys,
+// L = 128: 4.41 ms (5.40); 8 x 8192 keys, L = 64, mostly set-up: 40 us (64).
+
 #include "bpc_internal.h"
 #include "mfma_split.h"
 
 namespace bpc {
 
-// 64 keys per wavefront per iteration; four wavefronts per workgroup, eight
-// at L = 128, where one workgroup fills a CU's LDS
+// 64 keys per wavefront per iteration; eight wavefronts per workgroup at
+// L >= 64, where one workgroup takes most of a CU's LDS, else four
 template <int L>
-constexpr int hm_threads() { return L == 128 ? 512 : 256; }
+constexpr int hm_threads() { return L >= 64 ? 512 : 256; }
+// Up to L = 64 the bf16 parts of P (and of the Gram entries the matrix-core
+// corrections read) are kept in LDS in operand order beside the fp32 P, cut
+// once per workgroup; at L = 128 they do not fit and every wavefront cuts them
+// again for each 64 keys.  Cutting them each time was 1200 of 4300 vector
+// instructions per 64 keys at L = 64.
+template <int L>
+constexpr bool hm_parts() { return L <= 64; }
 constexpr int kHmPsStride = 132;     // fp32 P row stride in LDS (floats)
 constexpr int kHmXsStride = 20;      // transpose buffer row stride (floats)
 
@@ -141,12 +162,66 @@ __device__ __forceinline__ uint4 sign_operand(uint32_t byte, bool on) {
   return make_uint4(w[0], w[1], w[2], w[3]);
 }
 
+// All decisions of 64 keys in the reference arithmetic, for tiles in which many
+// are uncertain: four lanes per key, lane q of a quad holding the fp64
+// residual of coordinates [32 q, 32 q + 32), 16 keys at a time.  Writes the
+// code words and returns the lane's count of fragile decisions.
+template <int L>
+__device__ __forceinline__ unsigned int hm_reference_tile(const uint16_t* Kb, int64_t sK_n, int base, int key_end,
+                                                          const float* Ps, uint32_t* Cb) {
+  constexpr int W = L / 32;
+  const int lane = threadIdx.x & 63, qd = lane & 3;
+  unsigned int nfrag = 0;
+#pragma unroll 1
+  for (int pass = 0; pass < 4; ++pass) {
+    const int key = base + 16 * pass + (lane >> 2);
+    const bool valid = key < key_end;
+    const uint16_t* row = Kb + (int64_t)(valid ? key : base) * sK_n + 32 * qd;
+    double r[32];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const uint4 v = *reinterpret_cast<const uint4*>(row + 8 * q);
+      const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        r[8 * q + e] = bf16_to_f64((uint16_t)((e & 1) ? (w[e >> 1] >> 16) : (w[e >> 1] & 0xFFFFu)));
+    }
+    uint32_t word = 0u;
+#pragma unroll 1
+    for (int i = 0; i < L; ++i) {
+      const float* p = Ps + i * kHmPsStride + 32 * qd;
+      double acc = 0.0;
+#pragma unroll
+      for (int e = 0; e < 32; ++e) acc = dadd(acc, dmul(r[e], (double)p[e]));
+      const double s01 = dadd(acc, __shfl_xor(acc, 1, 64));
+      const double a = dadd(s01, __shfl_xor(s01, 2, 64));
+      const bool u = a >= 0.0;
+      if (qd == 0 && valid && fragile_decision(a)) ++nfrag;
+      if ((i >> 5) == qd && u) word |= 1u << (i & 31);
+      const double sg = u ? -1.0 : 1.0;
+#pragma unroll
+      for (int e = 0; e < 32; ++e) r[e] = __builtin_fma(sg, (double)p[e], r[e]);
+    }
+    if (valid && qd < W) Cb[(int64_t)key * W + qd] = word;
+  }
+  return nfrag;
+}
+// uncertain keys in one block of 16 bits above which the tile is done so
+constexpr int kHmMany = 24;
+
+typedef double f64x4_t __attribute__((ext_vector_type(4)));
+
 template <int L>
 struct HmShared {
   float Ps[L * kHmPsStride];              // P of this (b, h), fp32
   float Gs[hm_gram_size<L>()];            // fp32(P_t . P_i) for t < i, at hm_gram_at(t, i)
-  float4 cst[L];                          // per bit: |P_i|, c1, c2, c3 (see hm_bound)
+  float2 cst[L];                          // per bit: e1, e3 of the bound |k| e1 + e3 on |a^|
+  uint32_t emax[2];                       // their maxima, as bits
+  uint4 Pp[hm_parts<L>() ? (L / 16) * 4 * 3 * 64 : 1];   // parts of P: ((T 4 + m) 3 + part) 64 + lane
+  uint4 Gp[L == 64 ? 4 * 3 * 64 : 1];     // parts of G: ((T T / 4 + st) 3 + part) 64 + lane
   float Xs[hm_threads<L>() / 64][64 * kHmXsStride];  // per wavefront: MFMA tile -> one key per lane (also setup scratch)
+  double fb[hm_threads<L>() / 64][kHeadDim];  // per wavefront: the products of one reference decision
+  unsigned int nzero;                     // zero rows of P
   unsigned int nfrag, nfall;
 };
 
@@ -173,42 +248,68 @@ __global__ __launch_bounds__(hm_threads<L>(), 2) void hash_mm_kernel(const uint1
     const int i = e >> 5, c = e & 31;
     *reinterpret_cast<float4*>(&sh.Ps[i * kHmPsStride + 4 * c]) = reinterpret_cast<const float4*>(Pb)[e];
   }
-  if (tid == 0) sh.nfrag = 0, sh.nfall = 0;
+  if (tid == 0) sh.nfrag = 0, sh.nfall = 0, sh.nzero = 0, sh.emax[0] = 0u, sh.emax[1] = 0u;
   __syncthreads();
   double* Ad = reinterpret_cast<double*>(&sh.Xs[0][0]);  // sum_t |P_td|, [128]
   double* nP = Ad + kHeadDim;                             // |P_t| in fp64, [L]
-  for (int e = tid; e < L * L; e += kHmThreads) {
-    const int t = e / L, i = e % L;
-    if (t < i) {
-      double s = 0.0;
-      for (int d = 0; d < kHeadDim; d += 4) {
-        const float4 x = *reinterpret_cast<const float4*>(&sh.Ps[t * kHmPsStride + d]);
-        const float4 y = *reinterpret_cast<const float4*>(&sh.Ps[i * kHmPsStride + d]);
-        s = fma((double)x.x, (double)y.x, s);
-        s = fma((double)x.y, (double)y.y, s);
-        s = fma((double)x.z, (double)y.z, s);
-        s = fma((double)x.w, (double)y.w, s);
+  {
+    // The Gram matrix on the fp64 matrix cores: one 16 x 16 block (a, b), a <= b,
+    // per wavefront and turn; lane l supplies row l % 16 and coordinate 4 k +
+    // l / 16 of either operand and holds rows 4 j + l / 16 of column l % 16.
+    constexpr int nb = L / 16;
+    const int r16 = lane & 15, k4 = lane >> 4;
+    for (int pr = wave; pr < nb * (nb + 1) / 2; pr += NWV) {
+      int ba = 0, off = pr;
+      while (off >= nb - ba) off -= nb - ba, ++ba;
+      const int bb = ba + off;
+      const float* pa = &sh.Ps[(16 * ba + r16) * kHmPsStride + k4];
+      const float* pb = &sh.Ps[(16 * bb + r16) * kHmPsStride + k4];
+      f64x4_t g = (f64x4_t){0.0, 0.0, 0.0, 0.0};
+#pragma unroll 8
+      for (int k = 0; k < kHeadDim; k += 4)
+        g = __builtin_amdgcn_mfma_f64_16x16x4f64((double)pa[k], (double)pb[k], g, 0, 0, 0);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int t = 16 * ba + 4 * j + k4, i = 16 * bb + r16;
+        if (t < i) sh.Gs[hm_gram_at<L>(t, i)] = (float)g[j];
       }
-      sh.Gs[hm_gram_at<L>(t, i)] = (float)s;
     }
   }
-  if (tid < kHeadDim) {
+  // sum_t |P_td| and |P_t|: several lanes of a wavefront each
+  {
+    constexpr int S = kHmThreads / kHeadDim;
+    const int d = tid / S, s = tid % S;
     double a = 0.0;
-    for (int t = 0; t < L; ++t) a += fabs((double)sh.Ps[t * kHmPsStride + tid]);
-    Ad[tid] = a;
-  } else if (tid - kHeadDim < L) {
-    const int t = tid - kHeadDim;
-    double s = 0.0;
-    for (int d = 0; d < kHeadDim; ++d) s = fma((double)sh.Ps[t * kHmPsStride + d], (double)sh.Ps[t * kHmPsStride + d], s);
-    nP[t] = sqrt(s) * (1.0 + 0x1p-40);
+#pragma unroll 4
+    for (int t = s; t < L; t += S) a += fabs((double)sh.Ps[t * kHmPsStride + d]);
+#pragma unroll
+    for (int o = 1; o < S; o <<= 1) a += __shfl_xor(a, o, 64);
+    if (s == 0) Ad[d] = a;
+  }
+  constexpr int SB = kHmThreads / L;  // lanes per bit
+  {
+    const int t = tid / SB, s = tid % SB;
+    double a = 0.0;
+#pragma unroll 4
+    for (int d = s; d < kHeadDim; d += SB) {
+      const double x = (double)sh.Ps[t * kHmPsStride + d];
+      a = fma(x, x, a);
+    }
+#pragma unroll
+    for (int o = 1; o < SB; o <<= 1) a += __shfl_xor(a, o, 64);
+    if (s == 0) nP[t] = sqrt(a) * (1.0 + 0x1p-40);
   }
   __syncthreads();
-  if (tid < L) {
-    const int i = tid;
-    double cabs = 0.0, q = 0.0;
-    for (int t = 0; t < i; ++t)
-      cabs += fabs((double)sh.Gs[hm_gram_at<L>(t, i)]) + 0x1p-20 * nP[t] * nP[i];
-    for (int d = 0; d < kHeadDim; ++d) q += Ad[d] * fabs((double)sh.Ps[i * kHmPsStride + d]);
+  const int cbit = tid / SB, csub = tid % SB;
+  double cabs = 0.0, q = 0.0;
+  for (int t = csub; t < cbit; t += SB)
+    cabs += fabs((double)sh.Gs[hm_gram_at<L>(t, cbit)]) + 0x1p-20 * nP[t] * nP[cbit];
+#pragma unroll 4
+  for (int d = csub; d < kHeadDim; d += SB) q += Ad[d] * fabs((double)sh.Ps[cbit * kHmPsStride + d]);
+#pragma unroll
+  for (int o = 1; o < SB; o <<= 1) cabs += __shfl_xor(cabs, o, 64), q += __shfl_xor(q, o, 64);
+  if (csub == 0) {
+    const int i = cbit;
     const double up = 1.0 + 0x1p-20;
     // with the corrections on the matrix cores: two more roundings of
     // 2^-7-sized sums per earlier bit in the mid/lo chain (+2 u S, +2 u C_i)
@@ -218,30 +319,74 @@ __global__ __launch_bounds__(hm_threads<L>(), 2) void hash_mm_kernel(const uint1
     const double c3 = ((i + (mm ? 4.0 : 2.0)) * 0x1p-24 * 2.01 * cabs + q * (36.0 + i) * 0x1p-53 +
                        (mm ? 0x1p-109 : 0x1p-110) + 1.01e-6) *
                       up;
-    sh.cst[i] = make_float4((float)(nP[i] * up) * (float)up, (float)c1, (float)c2, (float)c3);
+    // |a^| > (|k| (|P_i| c1 + 2^-100) + c2 |a^| + c3) (1 + 2^-8), solved for |a^|
+    const double f = (1.0 + 0x1p-8) / (1.0 - c2 * (1.0 + 0x1p-8)) * up;
+    const float e1 = (float)((nP[i] * up * c1 + 0x1p-100) * f * up), e3 = (float)(c3 * f * up);
+    sh.cst[i] = make_float2(e1, e3);
+    // A zero row of P gives a = +0 for every finite key: u = +1 and fragile,
+    // counted per key below.  A bound below zero lets it pass as certain (and
+    // not when |k| is infinite or NaN).
+    if (nP[i] == 0.0) {
+      sh.cst[i] = make_float2(0.f, -3e38f);
+      atomicAdd(&sh.nzero, 1u);
+    } else {
+      // (infinite and NaN bounds have the largest bits)
+      atomicMax(&sh.emax[0], __float_as_uint(e1) & 0x7FFFFFFFu);
+      atomicMax(&sh.emax[1], __float_as_uint(e3) & 0x7FFFFFFFu);
+    }
+  }
+  if constexpr (hm_parts<L>()) {
+    for (int e = tid; e < (L / 16) * 4 * 64; e += kHmThreads) {
+      const int l = e & 63, m = (e >> 6) & 3, T = e >> 8;
+      const float* prow = &sh.Ps[(16 * T + (l & 15)) * kHmPsStride + 32 * m + 8 * (l >> 4)];
+      uint4* o = &sh.Pp[(T * 4 + m) * 3 * 64 + l];
+      split3(*reinterpret_cast<const float4*>(prow), *reinterpret_cast<const float4*>(prow + 4), o[0], o[64], o[128]);
+    }
+  }
+  if constexpr (L == 64) {
+    for (int e = tid; e < 4 * 64; e += kHmThreads) {
+      const int l = e & 63, s = e >> 6, T = s < 2 ? s + 1 : 3, st = s == 3 ? 1 : 0;
+      const int t0 = 32 * st + 8 * (l >> 4);
+      float4 x = make_float4(0.f, 0.f, 0.f, 0.f), y = x;
+      if (t0 < 16 * T) {
+        const float* gp = &sh.Gs[hm_gram_col<L>(16 * T + (l & 15)) + t0];
+        x = *reinterpret_cast<const float4*>(gp), y = *reinterpret_cast<const float4*>(gp + 4);
+      }
+      uint4* o = &sh.Gp[s * 3 * 64 + l];
+      split3(x, y, o[0], o[64], o[128]);
+    }
   }
   __syncthreads();
+  const float e1max = __uint_as_float(sh.emax[0]), e3max = __uint_as_float(sh.emax[1]);
 
   // ---- main loop: 64 keys per wavefront per iteration --------------------
   const int c16 = lane & 15, g4 = lane >> 4;
   float* Xs = sh.Xs[wave];
-  double* fb = reinterpret_cast<double*>(Xs);
+  double* fb = sh.fb[wave];
   const int key_begin = blockIdx.x * keys_per_wg;
   const int key_end = min(N, key_begin + keys_per_wg);
   unsigned int nfrag = 0, nfall = 0;
-  for (int base = key_begin + wave * 64; base < key_end; base += NWV * 64) {
-    // B operands: lane i holds key base + 16 tau + i % 16, coordinates
-    // 32 m + 8 (i / 16) .. + 7
-    uint4 kv[4][4];
-    float ss[4];
+  // B operands of a tile: lane i holds key base + 16 tau + i % 16, coordinates
+  // 32 m + 8 (i / 16) .. + 7
+  uint4 kv[4][4];
+  auto load_keys = [&](int base) {
 #pragma unroll
     for (int tau = 0; tau < 4; ++tau) {
       const int key = base + 16 * tau + c16;
+      const uint16_t* row = Kb + (int64_t)min(key, key_end - 1) * sK_n + 8 * g4;
+#pragma unroll
+      for (int m = 0; m < 4; ++m) kv[tau][m] = *reinterpret_cast<const uint4*>(row + 32 * m);
+    }
+  };
+  if (hm_parts<L>() && key_begin + wave * 64 < key_end) load_keys(key_begin + wave * 64);
+  for (int base = key_begin + wave * 64; base < key_end; base += NWV * 64) {
+    if constexpr (!hm_parts<L>()) load_keys(base);
+    float ss[4];
+#pragma unroll
+    for (int tau = 0; tau < 4; ++tau) {
       ss[tau] = 0.f;
 #pragma unroll
       for (int m = 0; m < 4; ++m) {
-        kv[tau][m] = key < key_end ? *reinterpret_cast<const uint4*>(Kb + (int64_t)key * sK_n + 32 * m + 8 * g4)
-                                   : make_uint4(0u, 0u, 0u, 0u);
         const uint32_t wv[4] = {kv[tau][m].x, kv[tau][m].y, kv[tau][m].z, kv[tau][m].w};
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -256,63 +401,83 @@ __global__ __launch_bounds__(hm_threads<L>(), 2) void hash_mm_kernel(const uint1
     // from here on lane l owns key base + l (its norm sits in ss[l / 16])
     const float ssq = g4 == 0 ? ss[0] : g4 == 1 ? ss[1] : g4 == 2 ? ss[2] : ss[3];
     const float nk = sqrtf(ssq * (1.f + 0x1p-14f)) * (1.f + 0x1p-20f);
-    const float nkx = nk * 0x1p-100f;
+    // bounds that reach 1e30 (or are not numbers) certify nothing
+    const float nkb = fmaf(nk, e1max, e3max) < 1e30f ? nk : __builtin_inff();
     const bool valid = base + lane < key_end;
     const uint16_t* my_row = Kb + (int64_t)(base + lane) * sK_n;
     uint32_t cw[W];
 #pragma unroll
     for (int w = 0; w < W; ++w) cw[w] = 0u;
+    unsigned int tfrag = valid && nk < 3.4e38f ? sh.nzero : 0u, tfall = 0;
+    bool many = false;
 
 #pragma unroll
     for (int T = 0; T < L / 16; ++T) {
+      if (many) break;
       // projections of bits 16 T .. 16 T + 15 of the 64 keys
-      f32x4_t ah[4], as[4], ch[4];
+      // (up to L = 64 two halves of the tile in turn, to halve the accumulators;
+      // at L = 128 that would cut P and G twice)
+      constexpr int HT = hm_parts<L>() ? 2 : 4;
 #pragma unroll
-      for (int tau = 0; tau < 4; ++tau) ah[tau] = as[tau] = ch[tau] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+      for (int hf = 0; hf < 4; hf += HT) {
+        f32x4_t ah[HT], as[HT], ch[HT];
 #pragma unroll
-      for (int m = 0; m < 4; ++m) {
-        const float* prow = &sh.Ps[(16 * T + c16) * kHmPsStride + 32 * m + 8 * g4];
-        uint4 phi, pmid, plo;
-        split3(*reinterpret_cast<const float4*>(prow), *reinterpret_cast<const float4*>(prow + 4), phi, pmid, plo);
+        for (int x = 0; x < HT; ++x) ah[x] = as[x] = ch[x] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int tau = 0; tau < 4; ++tau) {
-          as[tau] = mfma32(plo, kv[tau][m], as[tau]);
-          as[tau] = mfma32(pmid, kv[tau][m], as[tau]);
-          ah[tau] = mfma32(phi, kv[tau][m], ah[tau]);
-        }
-      }
-      if constexpr (hm_mm_corr<L>()) {
-        // The corrections by earlier blocks as one more contraction: D[j][key]
-        // = sum_{t < 16 T} fp32(G[t][16 T + j]) s_t(key), s_t = -1 where bit t
-        // of the key is set, else +1 (exact in bf16).  Gram entries are cut
-        // into hi + mid + lo like P; the hi products go to their own chain
-        // ch (sums of size C_i), mid and lo to the small chain as.
-#pragma unroll
-        for (int st = 0; st < (T + 1) / 2; ++st) {
-          const uint32_t cws = cw[st];
-          // lane (g4, c16): A = G[32 st + 8 g4 .. + 7][16 T + c16], B = signs of
-          // the same 8 bits of key 16 tau + c16 (none past 16 T)
-          const bool on = 32 * st + 8 * g4 < 16 * T;
-          uint4 ghi = make_uint4(0u, 0u, 0u, 0u), gmid = ghi, glo = ghi;
-          if (on) {
-            const float* gp = &sh.Gs[hm_gram_col<L>(16 * T + c16) + 32 * st + 8 * g4];
-            split3(*reinterpret_cast<const float4*>(gp), *reinterpret_cast<const float4*>(gp + 4), ghi, gmid, glo);
+        for (int m = 0; m < 4; ++m) {
+          uint4 phi, pmid, plo;
+          if constexpr (hm_parts<L>()) {
+            const uint4* pp = &sh.Pp[(T * 4 + m) * 3 * 64 + lane];
+            phi = pp[0], pmid = pp[64], plo = pp[128];
+          } else {
+            const float* prow = &sh.Ps[(16 * T + c16) * kHmPsStride + 32 * m + 8 * g4];
+            split3(*reinterpret_cast<const float4*>(prow), *reinterpret_cast<const float4*>(prow + 4), phi, pmid, plo);
           }
 #pragma unroll
-          for (int tau = 0; tau < 4; ++tau) {
-            const uint32_t word = (uint32_t)__shfl((int)cws, 16 * tau + c16, 64);
-            const uint4 sb = sign_operand((word >> (8 * g4)) & 0xFFu, on);
-            ch[tau] = mfma32(ghi, sb, ch[tau]);
-            as[tau] = mfma32(gmid, sb, as[tau]);
-            as[tau] = mfma32(glo, sb, as[tau]);
+          for (int x = 0; x < HT; ++x) {
+            as[x] = mfma32(plo, kv[hf + x][m], as[x]);
+            as[x] = mfma32(pmid, kv[hf + x][m], as[x]);
+            ah[x] = mfma32(phi, kv[hf + x][m], ah[x]);
           }
         }
-      }
+        if constexpr (hm_mm_corr<L>()) {
+          // The corrections by earlier blocks as one more contraction: D[j][key]
+          // = sum_{t < 16 T} fp32(G[t][16 T + j]) s_t(key), s_t = -1 where bit t
+          // of the key is set, else +1 (exact in bf16).  Gram entries are cut
+          // into hi + mid + lo like P; the hi products go to their own chain
+          // ch (sums of size C_i), mid and lo to the small chain as.
 #pragma unroll
-      for (int tau = 0; tau < 4; ++tau)
-        *reinterpret_cast<float4*>(&Xs[(16 * tau + c16) * kHmXsStride + 4 * g4]) =
-            make_float4((ah[tau][0] + as[tau][0]) + ch[tau][0], (ah[tau][1] + as[tau][1]) + ch[tau][1],
-                        (ah[tau][2] + as[tau][2]) + ch[tau][2], (ah[tau][3] + as[tau][3]) + ch[tau][3]);
+          for (int st = 0; st < (T + 1) / 2; ++st) {
+            const uint32_t cws = cw[st];
+            // lane (g4, c16): A = G[32 st + 8 g4 .. + 7][16 T + c16], B = signs of
+            // the same 8 bits of key 16 tau + c16 (none past 16 T)
+            const bool on = 32 * st + 8 * g4 < 16 * T;
+            uint4 ghi = make_uint4(0u, 0u, 0u, 0u), gmid = ghi, glo = ghi;
+            if constexpr (L == 64) {
+              const uint4* gp = &sh.Gp[(T * T / 4 + st) * 3 * 64 + lane];
+              ghi = gp[0], gmid = gp[64], glo = gp[128];
+            } else if (on) {
+              const float* gp = &sh.Gs[hm_gram_col<L>(16 * T + c16) + 32 * st + 8 * g4];
+              split3(*reinterpret_cast<const float4*>(gp), *reinterpret_cast<const float4*>(gp + 4), ghi, gmid, glo);
+            }
+#pragma unroll
+            for (int x = 0; x < HT; ++x) {
+              const uint32_t word = (uint32_t)__shfl((int)cws, 16 * (hf + x) + c16, 64);
+              const uint4 sb = sign_operand((word >> (8 * g4)) & 0xFFu, on);
+              ch[x] = mfma32(ghi, sb, ch[x]);
+              as[x] = mfma32(gmid, sb, as[x]);
+              as[x] = mfma32(glo, sb, as[x]);
+            }
+          }
+        }
+#pragma unroll
+        for (int x = 0; x < HT; ++x)
+          *reinterpret_cast<float4*>(&Xs[(16 * (hf + x) + c16) * kHmXsStride + 4 * g4]) =
+              make_float4((ah[x][0] + as[x][0]) + ch[x][0], (ah[x][1] + as[x][1]) + ch[x][1],
+                          (ah[x][2] + as[x][2]) + ch[x][2], (ah[x][3] + as[x][3]) + ch[x][3]);
+      }
+      // the next tile's keys are on their way while the last block is decided
+      if (hm_parts<L>() && T == L / 16 - 1 && base + NWV * 64 < key_end) load_keys(base + NWV * 64);
       wave_lds_sync();
       float y[16];
 #pragma unroll
@@ -320,7 +485,6 @@ __global__ __launch_bounds__(hm_threads<L>(), 2) void hash_mm_kernel(const uint1
         const float4 v = *reinterpret_cast<const float4*>(&Xs[lane * kHmXsStride + 4 * q]);
         y[4 * q] = v.x, y[4 * q + 1] = v.y, y[4 * q + 2] = v.z, y[4 * q + 3] = v.w;
       }
-      wave_lds_sync();
       // corrections by the bits of earlier blocks: y_j -= u_t Gr[t][j]
       // (on the vector units at L = 32)
 #pragma unroll
@@ -348,40 +512,45 @@ __global__ __launch_bounds__(hm_threads<L>(), 2) void hash_mm_kernel(const uint1
       // the reference arithmetic, lowest bit first, and kept as overrides.
       // Where a speculated sign was wrong, the block's later bits of that key
       // rested on it, and the block is run again with the overrides.
-      const float y0[16] = {y[0], y[1], y[2],  y[3],  y[4],  y[5],  y[6],  y[7],
-                            y[8], y[9], y[10], y[11], y[12], y[13], y[14], y[15]};
-      uint32_t ovm = 0u, ovv = 0u, ub = 0u;
-      while (true) {
-        uint32_t unc = 0u;
-        ub = 0u;
+      // (Its start is the lane's row of Xs, written back where the corrections
+      // of earlier blocks were added above.)
+      if (!hm_mm_corr<L>() && T > 0) {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) y[i] = y0[i];
+        for (int q = 0; q < 4; ++q)
+          *reinterpret_cast<float4*>(&Xs[lane * kHmXsStride + 4 * q]) =
+              make_float4(y[4 * q], y[4 * q + 1], y[4 * q + 2], y[4 * q + 3]);
+      }
+      // First with every sign taken from a^ (its sign bit: a certain a^ is not
+      // zero, and a^ of a zero row is +0), the uncertain ones collected beside.
+      uint32_t neg = 0u, unc = 0u;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const int bit = 16 * T + i;
-          const float4 cb = sh.cst[bit];
-          const float a = y[i];
-          const float E = fmaf(nk * cb.x, cb.y, fmaf(cb.z, fabsf(a), cb.w + nkx)) * (1.f + 0x1p-8f);
-          const bool sure = !valid || (fabsf(a) > E && E < 1e30f);
-          bool u = a >= 0.f;
-          if ((ovm >> i) & 1u) u = (ovv >> i) & 1u;
-          else if (!sure) unc |= 1u << i;
-          ub |= (u ? 1u : 0u) << i;
-          if (i < 15) {
-            const float sg = u ? -1.f : 1.f;
-            const float4* gr = reinterpret_cast<const float4*>(&sh.Gs[hm_gram_diag<L>(bit)]);
+      for (int i = 0; i < 16; ++i) {
+        const int bit = 16 * T + i;
+        const float2 cb = sh.cst[bit];
+        const float a = y[i];
+        neg = __builtin_amdgcn_alignbit(neg, __float_as_uint(a), 31);
+        unc = unc + unc + (fabsf(a) > fmaf(nkb, cb.x, cb.y) ? 0u : 1u);
+        if (i < 15) {
+          const float s = __uint_as_float((__float_as_uint(a) & 0x80000000u) | 0x3F800000u);
+          const float4* gr = reinterpret_cast<const float4*>(&sh.Gs[hm_gram_diag<L>(bit)]);
 #pragma unroll
-            for (int q = (i + 1) / 4; q < 4; ++q) {
-              const float4 g = gr[q];
-              const float gv[4] = {g.x, g.y, g.z, g.w};
+          for (int q = (i + 1) / 4; q < 4; ++q) {
+            const float4 g = gr[q];
+            const float gv[4] = {g.x, g.y, g.z, g.w};
 #pragma unroll
-              for (int e = 0; e < 4; ++e)
-                if (4 * q + e > i) y[4 * q + e] = fmaf(sg, gv[e], y[4 * q + e]);
-            }
+            for (int e = 0; e < 4; ++e)
+              if (4 * q + e > i) y[4 * q + e] = fmaf(-s, gv[e], y[4 * q + e]);
           }
         }
+      }
+      uint32_t ub = __brev(~neg) >> 16;
+      unc = valid ? __brev(unc) >> 16 : 0u;
+      uint32_t ovm = 0u, ovv = 0u;
+      while (true) {
         unsigned long long todo = __ballot(unc != 0u);
         if (!todo) break;
+        many = __popcll(todo) > kHmMany;
+        if (many) break;
         bool rerun = false;
         while (todo) {
           const int j = __ffsll((long long)todo) - 1;
@@ -402,11 +571,11 @@ __global__ __launch_bounds__(hm_threads<L>(), 2) void hash_mm_kernel(const uint1
             uj &= uj - 1;
             const double ae = hm_reference_decision(krow, sh.Ps, 16 * T + i0, uw[0], uw[1], uw[2], uw[3], fb);
             const bool uref = ae >= 0.0;
-            ++nfall;
+            ++tfall;
             if (lane == j) {
               ovm |= 1u << i0;
               ovv |= (uref ? 1u : 0u) << i0;
-              nfrag += fragile_decision(ae) ? 1u : 0u;
+              tfrag += fragile_decision(ae) ? 1u : 0u;
             }
             if (uref != (((ubj >> i0) & 1u) != 0u)) {
               rerun = true;  // this key's later bits of the block rested on the wrong sign
@@ -415,9 +584,39 @@ __global__ __launch_bounds__(hm_threads<L>(), 2) void hash_mm_kernel(const uint1
           }
         }
         if (!rerun) break;
+        unc = 0u, ub = 0u;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const float4 v = *reinterpret_cast<const float4*>(&Xs[lane * kHmXsStride + 4 * q]);
+          y[4 * q] = v.x, y[4 * q + 1] = v.y, y[4 * q + 2] = v.z, y[4 * q + 3] = v.w;
+        }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const int bit = 16 * T + i;
+          const float2 cb = sh.cst[bit];
+          const float a = y[i];
+          const bool sure = !valid || fabsf(a) > fmaf(nkb, cb.x, cb.y);
+          bool u = a >= 0.f;
+          if ((ovm >> i) & 1u) u = (ovv >> i) & 1u;
+          else if (!sure) unc |= 1u << i;
+          ub |= (u ? 1u : 0u) << i;
+          if (i < 15) {
+            const float sg = u ? -1.f : 1.f;
+            const float* gr = &sh.Gs[hm_gram_diag<L>(bit)];
+#pragma unroll
+            for (int e = i + 1; e < 16; ++e) y[e] = fmaf(sg, gr[e], y[e]);
+          }
+        }
       }
       cw[(16 * T) >> 5] |= ub << ((16 * T) & 31);
+      wave_lds_sync();  // Xs is rewritten by the next block only after these reads
     }
+    if (many) {
+      nfrag += hm_reference_tile<L>(Kb, sK_n, base, key_end, sh.Ps, codes + b * sC_b + h * sC_h);
+      nfall += (unsigned int)min(64, key_end - base) * L;
+      continue;
+    }
+    nfrag += tfrag, nfall += tfall;
     if (valid) {
       uint32_t* cp = codes + b * sC_b + h * sC_h + (int64_t)(base + lane) * W;
       if constexpr (W == 1) cp[0] = cw[0];
@@ -447,9 +646,11 @@ static hipError_t launch_hash_mm_L(const uint16_t* K, int64_t sK_b, int64_t sK_h
                                    hipStream_t stream) {
   static_assert(sizeof(HmShared<L>) <= 160 * 1024, "LDS budget");
   constexpr int kHmThreads = hm_threads<L>();
-  // about 2048 workgroups in all, each over whole wavefront iterations
+  // about 2048 workgroups of four wavefronts, 1024 of eight, each over whole
+  // wavefront iterations
   const long long total = (long long)B * Hkv * N;
-  long long per = (total + 2047) / 2048;
+  constexpr long long kWgs = 2048 * 256 / kHmThreads;
+  long long per = (total + kWgs - 1) / kWgs;
   per = (per + kHmThreads - 1) / kHmThreads * kHmThreads;
   per = per < kHmThreads ? kHmThreads : per > 64 * kHmThreads ? 64 * kHmThreads : per;
   const int keys_per_wg = (int)per;

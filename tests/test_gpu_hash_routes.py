@@ -1,0 +1,102 @@
+"""hash_keys (codes on the matrix cores with certified signs, residual norms
+apart) and hash_keys_mm against the kernel of decode-time append, which keeps
+the residual of Algorithm 2 and decides every bit in the reference arithmetic:
+the same codes, norms and fragile counts bit for bit, over the forms in which
+certified decisions are rare.  (The append kernel is checked against the oracle
+in test_gpu_append.py.)"""
+import pytest
+import torch
+
+import paper_2608_04405_amd as bpc
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+def reference(K, P, N):
+    B, H, _, _ = K.shape
+    L = P.shape[-2]
+    kn = K[:, :, :N].contiguous()
+    Kc, Vc = torch.zeros_like(kn), torch.zeros_like(kn)
+    codes = torch.zeros(B, H, N, L // 32, dtype=torch.int32, device=DEV)
+    err = torch.empty(B, H, N, device=DEV)
+    frag = torch.zeros(1, dtype=torch.int64, device=DEV)
+    bpc.append_kv(kn, kn, Kc, Vc, codes, P, 0, err_out=err, fragile=frag)
+    return codes, err, int(frag)
+
+
+def check(K, P, N):
+    B, H = K.shape[:2]
+    L = P.shape[-2]
+    want, err0, frag0 = reference(K, P, N)
+    for mm in (False, True):
+        codes = torch.full((B, H, N + 2, L // 32), 0x5A5A5A5A, dtype=torch.int32, device=DEV)
+        err = torch.empty(B, H, N, device=DEV)
+        frag = torch.zeros(1, dtype=torch.int64, device=DEV)
+        fall = torch.zeros(1, dtype=torch.int64, device=DEV)
+        if mm:
+            bpc.hash_keys_mm(K, P, N=N, codes_out=codes, fragile=frag, fallbacks=fall)
+            assert 0 <= int(fall) <= B * H * N * L
+        else:
+            bpc.hash_keys(K, P, N=N, codes_out=codes, err_out=err, fragile=frag)
+            assert bool(((err == err0) | (err.isnan() & err0.isnan())).all())
+        assert torch.equal(codes[:, :, :N], want)
+        assert (codes[:, :, N:] == 0x5A5A5A5A).all()
+        assert int(frag) == frag0
+
+
+def inputs(N, L, B=1, H=2, seed=0):
+    g = torch.Generator(device=DEV).manual_seed(seed + L)
+    A = torch.randn(H, 8, 128, generator=g, device=DEV)
+    K = (torch.randn(B, H, N, 8, generator=g, device=DEV) @ A
+         + 0.1 * torch.randn(B, H, N, 128, generator=g, device=DEV)).to(torch.bfloat16)
+    P = torch.randn(B, H, L, 128, generator=g, device=DEV) * torch.linspace(1.0, 0.05, L, device=DEV).view(-1, 1)
+    return K, P
+
+
+# one key, a tile and its edges, a 256-key workgroup of the norms and its edges,
+# a wavefront's second tile
+@pytest.mark.parametrize("L,N", [(32, 1), (64, 63), (128, 65), (64, 256), (128, 257), (32, 255), (64, 1500)])
+def test_sizes(L, N):
+    print(f"[hash routes] L={L} N={N}", flush=True)
+    check(*inputs(N, L, B=2), N)
+
+
+@pytest.mark.parametrize("L", [32, 64, 128])
+@pytest.mark.parametrize("form", ["zero_rows", "zero_projection", "zero_keys", "exact_fit", "few_uncertain", "non_finite",
+                                  "huge", "tiny", "strided", "shared"])
+def test_forms(form, L):
+    print(f"[hash routes] {form} L={L}", flush=True)
+    N = 300
+    K, P = inputs(N, L, seed=7)
+    if form == "zero_rows":  # a head whose keys ran out of directions
+        P[:, :, L // 2:] = 0
+        P[:, :, 3] = 0
+    elif form == "zero_projection":
+        P.zero_()
+    elif form == "zero_keys":  # padding inside a cache
+        K[:, :, 40:200] = 0
+    elif form == "exact_fit":  # every residual reaches 0 and most decisions are exactly 0
+        P[:] = 0
+        P[:, :, 0, :64] = 1.5
+        P[:, :, 1, 64:] = 0.25
+        K = torch.cat([P[:, :, :1, :64].expand(1, 2, N, 64), P[:, :, 1:2, 64:].expand(1, 2, N, 64)], -1)
+        K = K.to(torch.bfloat16).contiguous()
+        P[:, :, 2:] = torch.randn_like(P[:, :, 2:])
+        P[:, :, 2:, ::2] = -P[:, :, 2:, 1::2]
+    elif form == "few_uncertain":  # single keys at zero among certain ones
+        K[:, :, ::50] = 0
+    elif form == "non_finite":
+        K[0, 0, 5, 1] = float("inf")
+        K[0, 1, 64, 127] = float("nan")
+        P[0, 1, 9, 0] = float("inf")
+    elif form == "huge":
+        K = (K.float() * 2.0 ** 100).to(torch.bfloat16)
+        P = P * 2.0 ** 20
+    elif form == "tiny":
+        K = (K.float() * 2.0 ** -120).to(torch.bfloat16)
+    elif form == "strided":
+        K = torch.zeros(1, N, 2, 144, dtype=torch.bfloat16, device=DEV).transpose(1, 2)[..., :128].copy_(K)
+    elif form == "shared":
+        P = P[0, 0].contiguous()
+    check(K, P, N - 13 if form == "strided" else N)
