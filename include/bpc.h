@@ -352,10 +352,20 @@ int bpc_decode_attention_per_head(const uint16_t* q,
  * serr_out  [B, Hkv, m] int32, contiguous: the selected key indices in
  *           ascending order (written)
  * Both pointers 4-byte aligned.  No workspace; one kernel launch (one
- * workgroup per (b, KV head) making four passes over its N errors).
+ * workgroup per (b, KV head); beyond 16384 errors, or m > 4096, it makes four
+ * passes over its N errors).
+ *
+ * bpc_select_hard_ws is the same selection with bpc_select_hard_workspace_bytes
+ * bytes of workspace (4-byte aligned; its contents on entry do not matter; 0
+ * bytes, and any pointer, where it would not help): segments of up to 16384
+ * errors first keep their own m largest, so that the errors are read once and
+ * by as many workgroups as there are segments; two or three launches.
  */
 int bpc_select_hard(const float* err, int64_t sE_b, int64_t sE_h, int B, int Hkv, int N, int m,
                     int32_t* serr_out, void* stream);
+size_t bpc_select_hard_workspace_bytes(int B, int Hkv, int N, int m);
+int bpc_select_hard_ws(const float* err, int64_t sE_b, int64_t sE_h, int B, int Hkv, int N, int m,
+                       int32_t* serr_out, void* workspace, size_t workspace_bytes, void* stream);
 
 /*
  * bpc_decode_attention_eas -- bpc_decode_attention with the Error-Aware

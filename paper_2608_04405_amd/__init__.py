@@ -9,6 +9,7 @@ library has not been built (``python -m paper_2608_04405_amd.build_lib``).
 
 from __future__ import annotations
 
+import contextlib
 import ctypes
 import math
 import os
@@ -92,6 +93,10 @@ _lib.bpc_dense_attention.argtypes = [_p, _p, _i64, _i64, _i64, _p, _i64, _i64, _
                                      ctypes.c_float, _p, _p, _sz, _p]
 _lib.bpc_select_hard.restype = _i
 _lib.bpc_select_hard.argtypes = [_p, _i64, _i64, _i, _i, _i, _i, _p, _p]
+_lib.bpc_select_hard_workspace_bytes.restype = _sz
+_lib.bpc_select_hard_workspace_bytes.argtypes = [_i, _i, _i, _i]
+_lib.bpc_select_hard_ws.restype = _i
+_lib.bpc_select_hard_ws.argtypes = [_p, _i64, _i64, _i, _i, _i, _i, _p, _p, _sz, _p]
 _lib.bpc_set_decode_path.restype = _i
 _lib.bpc_set_decode_path.argtypes = [_i]
 _lib.bpc_decode_slice_keys.restype = _i
@@ -555,8 +560,15 @@ def select_hard(err: torch.Tensor, m: int, N: Optional[int] = None, *, serr_out:
     _on_gpu(err, serr_out)
     if serr_out is None:
         serr_out = torch.empty(B, Hkv, m, dtype=torch.int32, device=err.device)
-    _check(_lib.bpc_select_hard(_ptr(err), err.stride(0), err.stride(1), B, Hkv, N, m, _ptr(serr_out),
-                                _stream(stream)),
+    size = int(_lib.bpc_select_hard_workspace_bytes(B, Hkv, N, m))
+    ws = None
+    if size:
+        # allocated on the stream that uses it, so that its memory is not
+        # reused elsewhere while the kernels run
+        with torch.cuda.stream(stream) if stream is not None else contextlib.nullcontext():
+            ws = torch.empty(size, dtype=torch.uint8, device=err.device)
+    _check(_lib.bpc_select_hard_ws(_ptr(err), err.stride(0), err.stride(1), B, Hkv, N, m, _ptr(serr_out),
+                                   _ptr(ws), size, _stream(stream)),
            "bpc_select_hard")
     return serr_out
 

@@ -502,8 +502,8 @@ int bpc_dense_attention(const uint16_t* q, const uint16_t* K, int64_t sK_b, int6
   return BPC_OK;
 }
 
-int bpc_select_hard(const float* err, int64_t sE_b, int64_t sE_h, int B, int Hkv, int N, int m, int32_t* serr_out,
-                    void* stream) {
+static int select_hard_impl(const float* err, int64_t sE_b, int64_t sE_h, int B, int Hkv, int N, int m,
+                            int32_t* serr_out, void* workspace, size_t workspace_bytes, bool with_ws, void* stream) {
   g_last_error[0] = 0;
   int st;
   if ((st = check_sizes(B, Hkv, N))) return st;
@@ -512,9 +512,32 @@ int bpc_select_hard(const float* err, int64_t sE_b, int64_t sE_h, int B, int Hkv
   if (!err || !serr_out) return fail(BPC_EINVAL, "err and serr_out are required");
   if (sE_b < 0 || sE_h < 0) return fail(BPC_EINVAL, "err strides must be >= 0");
   if (!aligned4(err) || !aligned4(serr_out)) return fail(BPC_EALIGN, "err and serr_out must be 4-byte aligned");
-  hipError_t e = launch_select_hard(err, sE_b, sE_h, B, Hkv, N, m, serr_out, static_cast<hipStream_t>(stream));
+  if (with_ws) {
+    const size_t need = select_hard_workspace_bytes(B, Hkv, N, m);
+    if (need && (!workspace || workspace_bytes < need))
+      return fail(BPC_EWORKSPACE, "workspace of %zu bytes given, %zu needed", workspace ? workspace_bytes : 0, need);
+    if (!aligned4(workspace)) return fail(BPC_EALIGN, "workspace must be 4-byte aligned");
+    if (!need) workspace = nullptr;
+  }
+  hipError_t e = launch_select_hard(err, sE_b, sE_h, B, Hkv, N, m, serr_out, workspace,
+                                    static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return hip_fail(e, "bpc_select_hard launch");
   return BPC_OK;
+}
+
+int bpc_select_hard(const float* err, int64_t sE_b, int64_t sE_h, int B, int Hkv, int N, int m, int32_t* serr_out,
+                    void* stream) {
+  return select_hard_impl(err, sE_b, sE_h, B, Hkv, N, m, serr_out, nullptr, 0, false, stream);
+}
+
+size_t bpc_select_hard_workspace_bytes(int B, int Hkv, int N, int m) {
+  if (B < 1 || Hkv < 1 || N < 1 || m < 0 || m > N) return 0;
+  return select_hard_workspace_bytes(B, Hkv, N, m);
+}
+
+int bpc_select_hard_ws(const float* err, int64_t sE_b, int64_t sE_h, int B, int Hkv, int N, int m, int32_t* serr_out,
+                       void* workspace, size_t workspace_bytes, void* stream) {
+  return select_hard_impl(err, sE_b, sE_h, B, Hkv, N, m, serr_out, workspace, workspace_bytes, true, stream);
 }
 
 // ---------------------------------------------------------------------------

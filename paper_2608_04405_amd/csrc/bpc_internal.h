@@ -170,8 +170,11 @@ struct DenseArgs {
 };
 hipError_t launch_dense(const DenseArgs& a);
 
+// ws: select_hard_workspace_bytes, or nullptr (one workgroup per (b, h) then
+// does the whole selection, unless N fits one segment)
+size_t select_hard_workspace_bytes(int B, int Hkv, int N, int m);
 hipError_t launch_select_hard(const float* err, int64_t sE_b, int64_t sE_h, int B, int Hkv, int N, int m,
-                              int32_t* out, hipStream_t stream);
+                              int32_t* out, void* ws, hipStream_t stream);
 
 // Decode-time append: the cache rows the new keys and values are copied to
 // (pointers already at the first new position).

@@ -1,0 +1,45 @@
+"""select_hard by segments against a sort in the same order (IEEE total order
+of float32, lowest index first among equals), at the edges of a segment, of
+the levels and of m, with ties, negative and non-finite errors."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2608_04405_amd as bpc
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+def expected(e, m):
+    u = e.view(np.uint32).astype(np.int64)
+    key = np.where(u & 0x80000000, 0xFFFFFFFF - u, u + 0x80000000)
+    return np.sort(np.lexsort((np.arange(len(e)), -key))[:m]).astype(np.int32)
+
+
+# one segment exactly and one key more; m of a whole small input; the largest m
+# of the segments and the first beyond; three levels
+@pytest.mark.parametrize("N,m", [(16384, 1), (16384, 4096), (1000, 1000), (16385, 66), (16385, 4096), (16385, 4097),
+                                 (40000, 800), (140001, 4096), (600000, 3000), (65536, 1)])
+@pytest.mark.parametrize("values", ["norms", "ties", "wide"])
+def test_segments(N, m, values):
+    print(f"[select tiles] N={N} m={m} {values}", flush=True)
+    rng = np.random.default_rng(N + m)
+    if values == "norms":
+        e = (6 + 0.6 * rng.standard_normal((1, 2, N))).astype(np.float32)
+    elif values == "ties":
+        e = rng.integers(0, 5, (1, 2, N)).astype(np.float32)
+        e[0, 1] = 2.5  # every key equal
+    else:
+        e = rng.integers(0, 2 ** 32, (1, 2, N), dtype=np.uint64).astype(np.uint32).view(np.float32)
+        e[0, 0, : N // 3] = rng.standard_normal(N // 3) * 1e-30
+    t = torch.from_numpy(np.concatenate([e, e[..., :3]], -1)).to(DEV)  # rows of N + 3
+    got = bpc.select_hard(t, m, N=N)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    got2 = bpc.select_hard(t, m, N=N, stream=side)
+    torch.cuda.synchronize()
+    for h in range(2):
+        want = expected(e[0, h], m)
+        assert np.array_equal(got[0, h].cpu().numpy(), want)
+        assert np.array_equal(got2[0, h].cpu().numpy(), want)
