@@ -294,8 +294,8 @@ int bpc_append_kv(const uint16_t* k_new, int64_t sKn_b, int64_t sKn_h, int64_t s
   cp.Kc = K + (int64_t)pos * sK_n, cp.sKc_b = sK_b, cp.sKc_h = sK_h, cp.sKc_n = sK_n;
   cp.Vn = v_new, cp.sVn_b = sVn_b, cp.sVn_h = sVn_h, cp.sVn_n = sVn_t;
   cp.Vc = V + (int64_t)pos * sV_n, cp.sVc_b = sV_b, cp.sVc_h = sV_h, cp.sVc_n = sV_n;
-  hipError_t e = launch_hash(k_new, sKn_b, sKn_h, sKn_t, B, Hkv, T, L, P, sP_b, sP_h, codes + (int64_t)pos * (L / 32),
-                             sC_b, sC_h, err_out, fragile_out, static_cast<hipStream_t>(stream), &cp);
+  hipError_t e = launch_append(k_new, sKn_b, sKn_h, sKn_t, B, Hkv, T, L, P, sP_b, sP_h,
+                               codes + (int64_t)pos * (L / 32), sC_b, sC_h, err_out, fragile_out, static_cast<hipStream_t>(stream), &cp);
   if (e != hipSuccess) return hip_fail(e, "bpc_append_kv launch");
   return BPC_OK;
 }

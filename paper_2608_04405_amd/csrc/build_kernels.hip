@@ -8,7 +8,10 @@
 
 #pragma clang fp contract(off)
 
+#include <type_traits>
+
 #include "bpc_internal.h"
+#include "mfma_split.h"
 
 namespace bpc {
 
@@ -430,10 +433,9 @@ hipError_t launch_norm(const uint16_t* K, int64_t sK_b, int64_t sK_h, int64_t sK
 // workgroup (padded rows avoid bank conflicts between the four blocks).
 // ============================================================================
 
-// With a cache copy (cp.Kc non-null), decode-time append: each key row of K
-// (the new keys) is also stored into the cache rows cp.Kc, and the matching
-// value rows cp.Vn into cp.Vc; the four lanes of a key each move a quarter
-// of both rows.
+// Each key row of K (the new keys) is also stored into the cache rows cp.Kc,
+// and the matching value rows cp.Vn into cp.Vc; the four lanes of a key each
+// move a quarter of both rows.
 template <int L>
 __global__ __launch_bounds__(256) void hash_kernel(const uint16_t* __restrict__ K, int64_t sK_b, int64_t sK_h,
                                                    int64_t sK_n, int Hkv, int N, const float* __restrict__ P,
@@ -470,7 +472,7 @@ __global__ __launch_bounds__(256) void hash_kernel(const uint16_t* __restrict__ 
       for (int e = 0; e < 8; ++e)
         r[8 * c + e] = bf16_to_f64((uint16_t)((e & 1) ? (w[e >> 1] >> 16) : (w[e >> 1] & 0xFFFFu)));
     }
-    if (cp.Kc) {
+    {
       uint16_t* kc = cp.Kc + b * cp.sKc_b + h * cp.sKc_h + (int64_t)key * cp.sKc_n + 32 * qd;
       const uint16_t* vn = cp.Vn + b * cp.sVn_b + h * cp.sVn_h + (int64_t)key * cp.sVn_n + 32 * qd;
       uint16_t* vc = cp.Vc + b * cp.sVc_b + h * cp.sVc_h + (int64_t)key * cp.sVc_n + 32 * qd;
@@ -520,11 +522,155 @@ __global__ __launch_bounds__(256) void hash_kernel(const uint16_t* __restrict__ 
   }
 }
 
-hipError_t launch_hash(const uint16_t* K, int64_t sK_b, int64_t sK_h, int64_t sK_n, int B, int Hkv, int N, int L,
+// ---------------------------------------------------------------------------
+// Decode-time append of a few tokens: one wavefront per new key, lane l holding
+// coordinates 2 l and 2 l + 1 of the fp64 residual and of every row of P (all
+// of its loads in flight at once).  With one key per quad of lanes, as above,
+// each bit is a chain of 32 dependent fp64 multiplies and additions, 64 bits of
+// it for one token.  Here the dot product is a wavefront sum in another order,
+// which differs from the reference by at most 2^-44 sum_d |r_d P_id| (164
+// roundings); outside that and the fragile threshold its sign is the
+// reference's, else the products are summed again in the reference order.  The
+// residual itself is the reference's.  16 x 8 heads, one token, L = 64: 16.6 us a
+// call (39.7).
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ double wave_sum_f64(double x) {
+  auto dpp_add = [](double v, auto ctrl) {
+    constexpr int C = decltype(ctrl)::value;
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), C, 0xF, 0xF, false);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), C, 0xF, 0xF, false);
+    return v + __hiloint2double(hi, lo);
+  };
+  x = dpp_add(x, std::integral_constant<int, 0xB1>{});   // lane ^ 1
+  x = dpp_add(x, std::integral_constant<int, 0x4E>{});   // lane ^ 2
+  x = dpp_add(x, std::integral_constant<int, 0x141>{});  // 7 - lane within 8
+  x = dpp_add(x, std::integral_constant<int, 0x140>{});  // 15 - lane within 16
+  {
+    const uint32_t lo = (uint32_t)__double2loint(x), hi = (uint32_t)__double2hiint(x);
+    const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    x = __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+  }
+  {
+    const uint32_t lo = (uint32_t)__double2loint(x), hi = (uint32_t)__double2hiint(x);
+    const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+    x = __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+  }
+  return x;
+}
+
+// ((b0 + b1) + (b2 + b3)) of the 128 values v0 (coordinate 2 l) and v1
+// (2 l + 1), each block of 32 summed in ascending order from +0
+__device__ __forceinline__ double ordered_sum_f64(double v0, double v1, double* fb) {
+  const int l = threadIdx.x & 63;
+  fb[2 * l] = v0, fb[2 * l + 1] = v1;
+  wave_lds_sync();
+  double s = 0.0;
+  if (l < 4)
+    for (int e = 0; e < 32; ++e) s = dadd(s, fb[32 * l + e]);
+  const double s0 = readlane_f64(s, 0), s1 = readlane_f64(s, 1), s2 = readlane_f64(s, 2), s3 = readlane_f64(s, 3);
+  wave_lds_sync();  // fb is rewritten by the next call only after these reads
+  return dadd(dadd(s0, s1), dadd(s2, s3));
+}
+
+template <int L>
+__global__ __launch_bounds__(64) void append_kernel(const uint16_t* __restrict__ K, int64_t sK_b, int64_t sK_h,
+                                                    int64_t sK_n, int Hkv, int N, const float* __restrict__ P,
+                                                    int64_t sP_b, int64_t sP_h, uint32_t* __restrict__ codes,
+                                                    int64_t sC_b, int64_t sC_h, float* __restrict__ err,
+                                                    unsigned long long* __restrict__ fragile, AppendCopy cp) {
+  constexpr int W = L / 32;
+  constexpr int C = L < 64 ? L : 64;  // rows of P held at a time
+  __shared__ double fb[kHeadDim];
+  const int lane = threadIdx.x, key = blockIdx.x;
+  const int bh = blockIdx.y, b = bh / Hkv, h = bh % Hkv;
+  const float2* Pl = reinterpret_cast<const float2*>(P + b * sP_b + h * sP_h) + lane;
+  const uint32_t kk = reinterpret_cast<const uint32_t*>(K + b * sK_b + h * sK_h + (int64_t)key * sK_n)[lane];
+  const uint32_t vv =
+      reinterpret_cast<const uint32_t*>(cp.Vn + b * cp.sVn_b + h * cp.sVn_h + (int64_t)key * cp.sVn_n)[lane];
+  double r0 = bf16_to_f64((uint16_t)(kk & 0xFFFFu)), r1 = bf16_to_f64((uint16_t)(kk >> 16));
+  float top = fmaxf(fabsf(bf16_to_f32(kk & 0xFFFFu)), fabsf(bf16_to_f32(kk >> 16)));
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) top = fmaxf(top, __shfl_xor(top, o, 64));
+  double rmax = (double)top;  // bounds every |r_d|, with the rows of P removed so far and in hand
+  uint32_t word[W];
+  int nfrag = 0;
+#pragma unroll
+  for (int w = 0; w < W; ++w) word[w] = 0u;
+#pragma unroll 1
+  for (int c = 0; c < L / C; ++c) {
+    float2 p[C];
+#pragma unroll
+    for (int i = 0; i < C; ++i) p[i] = Pl[(C * c + i) * (kHeadDim / 2)];
+    if (c == 0) {  // the copies, behind the loads of P
+      reinterpret_cast<uint32_t*>(cp.Kc + b * cp.sKc_b + h * cp.sKc_h + (int64_t)key * cp.sKc_n)[lane] = kk;
+      reinterpret_cast<uint32_t*>(cp.Vc + b * cp.sVc_b + h * cp.sVc_h + (int64_t)key * cp.sVc_n)[lane] = vv;
+    }
+    float pm = 0.f;
+#pragma unroll
+    for (int i = 0; i < C; ++i) pm = fmaxf(pm, fmaxf(fabsf(p[i].x), fabsf(p[i].y)));
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) pm = fmaxf(pm, __shfl_xor(pm, o, 64));
+    rmax += (double)C * (double)pm;
+    const double bound = 0x1p-44 * 128.0 * rmax * (double)pm + 1.01e-6;
+#pragma unroll
+    for (int i = 0; i < C; ++i) {
+      const double p0 = (double)p[i].x, p1 = (double)p[i].y;
+      double a = wave_sum_f64(__builtin_fma(r0, p0, r1 * p1));
+      if (!(fabs(a) > bound)) {
+        a = ordered_sum_f64(dmul(r0, p0), dmul(r1, p1), fb);
+        nfrag += fragile_decision(a) ? 1 : 0;
+      }
+      const bool u = a >= 0.0;
+      const double sg = u ? -1.0 : 1.0;
+      r0 = __builtin_fma(sg, p0, r0);
+      r1 = __builtin_fma(sg, p1, r1);
+#pragma unroll
+      for (int w = 0; w < W; ++w)
+        if (w == (C * c + i) >> 5) word[w] |= (u ? 1u : 0u) << (i & 31);
+    }
+  }
+  if (lane < W) {
+    uint32_t x = word[0];
+#pragma unroll
+    for (int w = 1; w < W; ++w) x = lane == w ? word[w] : x;
+    codes[b * sC_b + h * sC_h + (int64_t)key * W + lane] = x;
+  }
+  if (err) {
+    const double sq = ordered_sum_f64(dmul(r0, r0), dmul(r1, r1), fb);
+    if (lane == 0) err[(size_t)bh * N + key] = (float)sqrt(sq);
+  }
+  if (fragile && lane == 0 && nfrag) atomicAdd(fragile, (unsigned long long)nfrag);
+}
+
+// New keys per (b, h) up to which each gets a wavefront of its own; beyond,
+// sixteen keys per wavefront issue less in all (measured at 16 x 8 heads).
+constexpr int kAppendWaveKeys = 32;
+
+hipError_t launch_append(const uint16_t* K, int64_t sK_b, int64_t sK_h, int64_t sK_n, int B, int Hkv, int N, int L,
                        const float* P, int64_t sP_b, int64_t sP_h, uint32_t* codes, int64_t sC_b, int64_t sC_h,
                        float* err, unsigned long long* fragile, hipStream_t stream, const AppendCopy* append) {
   const dim3 grid((N + 63) / 64, B * Hkv);
-  const AppendCopy cp = append ? *append : AppendCopy{};
+  const AppendCopy cp = *append;
+  if (N <= kAppendWaveKeys) {
+    const dim3 waves(N, B * Hkv);
+    switch (L) {
+      case 32:
+        append_kernel<32><<<waves, 64, 0, stream>>>(K, sK_b, sK_h, sK_n, Hkv, N, P, sP_b, sP_h, codes, sC_b, sC_h, err,
+                                                    fragile, cp);
+        break;
+      case 64:
+        append_kernel<64><<<waves, 64, 0, stream>>>(K, sK_b, sK_h, sK_n, Hkv, N, P, sP_b, sP_h, codes, sC_b, sC_h, err,
+                                                    fragile, cp);
+        break;
+      default:
+        append_kernel<128><<<waves, 64, 0, stream>>>(K, sK_b, sK_h, sK_n, Hkv, N, P, sP_b, sP_h, codes, sC_b, sC_h,
+                                                     err, fragile, cp);
+        break;
+    }
+    return hipGetLastError();
+  }
   switch (L) {
     case 32:
       hash_kernel<32><<<grid, 256, 0, stream>>>(K, sK_b, sK_h, sK_n, Hkv, N, P, sP_b, sP_h, codes, sC_b, sC_h, err,
