@@ -136,7 +136,7 @@ def version() -> int:
 
 def set_decode_path(path: int) -> None:
     """0: a decode step runs as one fused launch whenever its workgroups fit
-    on the GPU at once (the default; 4096- or 8192-key slices where
+    on the GPU at once (the default; slices of 2048 to 8192 keys where
     16384-key ones would leave the GPU mostly idle); 1: always the three
     launches; 2: the fused launch on 16384-key slices only."""
     _check(_lib.bpc_set_decode_path(int(path)), "bpc_set_decode_path")
@@ -149,7 +149,7 @@ def decode_path_taken(B: int, Hq: int, Hkv: int, N: int, L: int) -> int:
 
 
 def decode_slice_keys(B: int, Hq: int, Hkv: int, N: int, L: int) -> int:
-    """Keys per slice (16384, 8192 or 4096) of a decode step of this shape on the
+    """Keys per slice (16384, 8192, 4096 or 2048) of a decode step of this shape on the
     current device (needs a GPU)."""
     return int(_lib.bpc_decode_slice_keys(B, Hq, Hkv, N, L))
 

@@ -74,12 +74,12 @@ static int check_opt_aligned(const char* name, const void* p) {
   return BPC_OK;
 }
 
-DecodeLayout decode_layout(int B, int Hq, int Hkv, int N, int L, int k) {
+DecodeLayout decode_layout(int B, int Hq, int Hkv, int N, int L, int k, int smallest) {
   DecodeLayout d{};
   const size_t BH = (size_t)B * Hkv;
   d.W = L / 32;
   d.G = Hq / Hkv;
-  const int fused_slice = decode_fused_slice(B, Hq, Hkv, N, L);
+  const int fused_slice = decode_fused_slice(B, Hq, Hkv, N, L, smallest);
   d.fused = fused_slice != 0;
   d.slice = d.fused ? fused_slice : kSlice;
   d.nslices = (N + d.slice - 1) / d.slice;
@@ -351,7 +351,10 @@ static int decode_impl(const uint16_t* q, const uint16_t* K, int64_t sK_b, int64
   }
   if (events && n_events != BPC_DECODE_STAGES + 1)
     return fail(BPC_EINVAL, "n_events=%d, expected %d", n_events, BPC_DECODE_STAGES + 1);
-  const DecodeLayout lay = decode_layout(B, Hq, Hkv, N, L, k);
+  DecodeLayout lay = decode_layout(B, Hq, Hkv, N, L, k);
+  // a workspace sized for larger slices runs on those
+  if (lay.fused && lay.slice == kSliceTiny && workspace_bytes < lay.total)
+    lay = decode_layout(B, Hq, Hkv, N, L, k, kSliceSmall);
   if (!workspace || workspace_bytes < lay.total)
     return fail(BPC_EWORKSPACE, "workspace of %zu bytes given, %zu needed", workspace ? workspace_bytes : 0,
                 lay.total);

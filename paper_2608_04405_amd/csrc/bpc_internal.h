@@ -24,6 +24,8 @@ constexpr int kSlice = 16384;
 // groups of up to 8 query heads).
 constexpr int kSliceMid = 8192;
 constexpr int kSliceSmall = 4096;
+// and on 2048 where even those leave most compute units without a workgroup
+constexpr int kSliceTiny = 2048;
 constexpr int kScoreThreads = 512;  // scoring workgroup: 32 keys per thread
 constexpr int kMaxSlices = 1024;
 // One attention workgroup per slice keeps its selected candidates, read in
@@ -99,7 +101,7 @@ constexpr int kQcodeStride = 64;
 // [B Hkv][k] int32.
 struct DecodeLayout {
   bool fused;
-  int slice;  // keys per slice (kSlice, or kSliceMid / kSliceSmall on the fused path)
+  int slice;  // keys per slice (kSlice, or kSliceMid / kSliceSmall / kSliceTiny on the fused path)
   int nslices, G, W;
   size_t off_cand, off_meta, off_hist_fine, off_hist_cc, off_win, off_part, off_qcode, total;
   size_t off_sync, off_pub, off_rows;
@@ -117,10 +119,11 @@ struct BuildLayout {
   size_t total_ck;  // with the room of an fp64 residual per key, which no build needs any more
 };
 
-DecodeLayout decode_layout(int B, int Hq, int Hkv, int N, int L, int k);
+// smallest: the smallest slice considered (more slices need more workspace)
+DecodeLayout decode_layout(int B, int Hq, int Hkv, int N, int L, int k, int smallest = kSliceTiny);
 // Keys per slice when the current device runs the decode step as the single
 // fused launch (every slice's workgroup resident at once), else 0.
-int decode_fused_slice(int B, int Hq, int Hkv, int N, int L);
+int decode_fused_slice(int B, int Hq, int Hkv, int N, int L, int smallest = kSliceTiny);
 inline bool decode_fused_ok(int B, int Hq, int Hkv, int N, int L) { return decode_fused_slice(B, Hq, Hkv, N, L) != 0; }
 // 0: automatic; 1: always the three-launch path; 2: the fused path only on
 // slices of kSlice keys (for comparisons)

@@ -2844,13 +2844,14 @@ static int fused_capacity_small(int L, int G) {
 }
 
 static int fused_capacity_of(int L, int G, int SL) {
+  if (SL == kSliceTiny) return fused_capacity_small<kSliceTiny>(L, G);
   if (SL == kSliceSmall) return fused_capacity_small<kSliceSmall>(L, G);
   if (SL == kSliceMid) return fused_capacity_small<kSliceMid>(L, G);
   if (SL != kSlice) return 0;
   return L == 32 ? fused_capacity_L<32, kSlice>(G) : L == 64 ? fused_capacity_L<64, kSlice>(G) : fused_capacity_L<128, kSlice>(G);
 }
 
-int decode_fused_slice(int B, int Hq, int Hkv, int N, int L) {
+int decode_fused_slice(int B, int Hq, int Hkv, int N, int L, int smallest) {
   const int path = g_decode_path.load();
   if (path == 1 || Hkv < 1 || Hq % Hkv || (int64_t)B * Hkv > kFusedMaxBH) return 0;
   const int G = Hq / Hkv;
@@ -2859,13 +2860,21 @@ int decode_fused_slice(int B, int Hq, int Hkv, int N, int L) {
   // unit (measured: batch 8 x 8 heads x 65536 keys 37.8 -> 34.7 us on 8192
   // keys, 40.9 on 4096; batch 1 x 8 heads x 32768 keys 35.4 -> 25.3 us on
   // 4096), fits on the device at once and keeps each (b, h) within the
-  // one-round threshold's 64 slices.
+  // one-round threshold's 64 slices.  A cache of one slice takes the smaller
+  // kernel too: its loops cover 4096 keys instead of 16384 (1 x 8 heads x 4096
+  // keys, L = 32: 24.8 -> 17.6 us).  Slices of 2048 pay while a (b, h) has at
+  // most 16 of them and the grid at most one workgroup per compute unit
+  // (against 4096: 1 x 8 heads x 4096 keys, L = 64, 20.7 -> 18.2 us; x 32768
+  // 21.7 -> 20.5; 4 x 8 x 16384 23.0 -> 20.3; beyond 16 the exchange between
+  // the slices costs more than they save: 1 x 8 x 131072 27.0 -> 33.4).
   if (path == 0 && small_slices_built(L, G)) {
     const int64_t ncu = device_cu_count();
-    for (const int sl : {kSliceSmall, kSliceMid}) {
+    for (const int sl : {kSliceTiny, kSliceSmall, kSliceMid}) {
+      if (sl < smallest) continue;
       const int64_t ns = (N + sl - 1) / sl;
       const int64_t nwg = (int64_t)B * Hkv * ns;
-      if (ns > 1 && ns <= kWinSlices && nwg <= 2 * ncu && nwg <= fused_capacity_of(L, G, sl)) return sl;
+      if (sl == kSliceTiny && (ns > 16 || nwg > ncu)) continue;
+      if (ns <= kWinSlices && nwg <= 2 * ncu && nwg <= fused_capacity_of(L, G, sl)) return sl;
     }
   }
   const int64_t nwg = (int64_t)B * Hkv * ((N + kSlice - 1) / kSlice);
@@ -2913,6 +2922,7 @@ static hipError_t launch_fused_L(const DecodeArgs& a, const DecodeLayout& lay) {
 
 hipError_t launch_decode(const DecodeArgs& a, const DecodeLayout& lay) {
   if (lay.fused) {
+    if (lay.slice == kSliceTiny) return a.L == 32 ? launch_fused_L<32, kSliceTiny>(a, lay) : launch_fused_L<64, kSliceTiny>(a, lay);
     if (lay.slice == kSliceSmall) return a.L == 32 ? launch_fused_L<32, kSliceSmall>(a, lay) : launch_fused_L<64, kSliceSmall>(a, lay);
     if (lay.slice == kSliceMid) return a.L == 32 ? launch_fused_L<32, kSliceMid>(a, lay) : launch_fused_L<64, kSliceMid>(a, lay);
     switch (a.L) {
