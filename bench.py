@@ -58,8 +58,8 @@ def parse():
                     help="summarize rocprofv3 csv output under each DIR (kernel stats and counters per dispatch) "
                          "instead of benchmarking")
     ap.add_argument("--prefill-only", metavar="WORKLOAD", default=None,
-                    help="time only the prefill of one layer of WORKLOAD: Algorithm 1 recomputing its residual, "
-                         "then with the residual checkpoint, then Algorithm 2 on both kernels; print one JSON line")
+                    help="time only the prefill of one layer of WORKLOAD: Algorithm 1 on either size of "
+                         "workspace, then Algorithm 2 by both entry points; print one JSON line")
     ap.add_argument("--pmc-json", metavar="PATH", default=None,
                     help="with --summarize over a FETCH_SIZE and a WRITE_SIZE run: write HBM bytes per launch")
     return ap.parse_args()
@@ -286,9 +286,9 @@ def measure_config(bpc, cfg, dev, n_inst, steps, warmup, log_name):
             hash_mm_ms += ev[2].elapsed_time(ev[3])
             build_ck_ms += ev[3].elapsed_time(ev[4])
             if not torch.equal(c2, c3):
-                raise RuntimeError(f"{log_name}: matrix-core Algorithm 2 codes differ from the fp64 kernel's")
+                raise RuntimeError(f"{log_name}: the two entry points of Algorithm 2 give different codes")
             if not (torch.equal(P4, P) and torch.equal(c4, codes)):
-                raise RuntimeError(f"{log_name}: the checkpointed Algorithm 1 build differs from the recomputing one")
+                raise RuntimeError(f"{log_name}: the Algorithm 1 builds on the two workspaces differ")
             del c2, c3, P4, c4
         data.append({"q": d["q"], "K": d["K"], "V": d["V"], "codes": codes, "P": P})
         del d
@@ -349,9 +349,8 @@ def copy_ceiling(dev):
 
 def prefill_only(name):
     """Prefill of one layer of a workload, each kernel path once after a
-    warm-up build: Algorithm 1 recomputing the residual, Algorithm 1 with
-    the residual checkpoint (results compared), Algorithm 2 fp64 and on the
-    matrix cores (codes compared)."""
+    warm-up build: Algorithm 1 on the default and on the larger workspace
+    (results compared), Algorithm 2 by both entry points (codes compared)."""
     import torch
 
     import paper_2608_04405_amd as bpc
@@ -443,7 +442,7 @@ def main():
             ev[3].record()
             codes4, _ = bpc.hash_keys(it["K"], P)
             ev[4].record()
-            # Algorithm 1 again, keeping the fp64 residual every 16 bits
+            # Algorithm 1 again, on the larger workspace
             del ws_build
             ws_ck = torch.empty(bpc.build_checkpoint_workspace_bytes(B, Hkv, N, L), dtype=torch.uint8, device=dev)
             err5 = torch.empty(B, Hkv, N, dtype=torch.float32, device=dev)
@@ -461,10 +460,10 @@ def main():
             hash_codes_ms = ev[3].elapsed_time(ev[4])
             build_ck_ms = ev5[0].elapsed_time(ev5[1])
             if not (torch.equal(codes2, codes3) and torch.equal(codes2, codes4)) or int(frag2.item()) != int(frag3.item()):
-                raise RuntimeError("matrix-core Algorithm 2 differs from the fp64 kernel")
+                raise RuntimeError("the two entry points of Algorithm 2 differ")
             if not (torch.equal(P5, P) and torch.equal(codes5, codes) and torch.equal(err5, err)
                     and int(frag5.item()) == int(frag.item())):
-                raise RuntimeError("the checkpointed Algorithm 1 build differs from the recomputing one")
+                raise RuntimeError("the Algorithm 1 builds on the two workspaces differ")
             keys = B * Hkv * N
             prefill = {"build_ms": round(build_ms, 3), "hash_ms": round(hash_ms, 3),
                        "build_keys_per_s": keys / (build_ms / 1e3), "hash_keys_per_s": keys / (hash_ms / 1e3),
@@ -477,10 +476,10 @@ def main():
                        "fragile_sign_decisions_build": int(frag.item()),
                        "fragile_sign_decisions_hash": int(frag2.item()),
                        "what": "Algorithm 1 (build P, codes and errors) and Algorithm 2 (hash every key, with "
-                               "errors) for the whole batch, fp64 fixed-order arithmetic; build_checkpoint: the same "
-                               "build keeping each key's fp64 residual every 16 bits (same results); hash_codes_only: the same "
-                               "kernel without the errors; hash_mm: the same codes with the projections on the "
-                               "matrix cores and certified signs (recomputed = decisions redone in fp64); fragile = "
+                               "errors) for the whole batch, the results of the fp64 fixed-order arithmetic; "
+                               "build_checkpoint: the same build on the larger workspace; hash_codes_only: Algorithm 2 "
+                               "without the errors; hash_mm: the same codes by bpc_hash_keys_mm "
+                               "(recomputed = decisions redone in fp64); fragile = "
                                "sign decisions with |a| < 1e-6"}
             del codes2, codes3, codes4, err2, ws_ck, P5, codes5, err5
             ws_build = None
