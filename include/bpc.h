@@ -144,7 +144,8 @@ int bpc_decode_path_taken(int B, int Hq, int Hkv, int N, int L);
  * key), 2 bytes per key and per-workgroup sums.  A smaller workspace, down to
  * one fp64 partial sum per 128-key chunk and coordinate plus fp64 copies of P
  * and G, is accepted as well: each pass then recomputes every R_j from the
- * key, its code bits so far and P, with the same results.
+ * key, its code bits so far and P, with the same results (as a call over at
+ * most 40960 keys does on any workspace, being faster there).
  * bpc_build_checkpoint_workspace_bytes gives 1 KiB more per key (the size of
  * an fp64 residual, rounded up to 128-key chunks); it is accepted like any
  * larger workspace and no longer makes a difference.

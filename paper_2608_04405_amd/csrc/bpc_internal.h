@@ -80,6 +80,7 @@ constexpr int kBuildChunk = 64 * kBuildGroups;     // keys per workgroup (one ch
 constexpr int kBuildFold = 32;
 // fp64 values per (b, h) and coordinate that the scanning build carries from bit to bit
 constexpr int kScanStats = 7;
+constexpr int kScanMinKeys = 40960;  // keys of the whole call up to which the rebuilding passes are faster
 constexpr int kScanWgs = 512;  // workgroups of one of its passes: two per compute unit, all resident
 
 // ---- workspace layouts -----------------------------------------------------

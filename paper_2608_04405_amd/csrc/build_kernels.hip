@@ -300,7 +300,11 @@ static void launch_build_W(const BuildArgs& a, const BuildLayout& lay, bool scan
 
 hipError_t launch_build(const BuildArgs& a, bool scan) {
   const BuildLayout lay = build_layout(a.B, a.Hkv, a.N, a.L);
-  scan = scan && a.sK_n < (1 << 24);  // its tiles of 64 rows are addressed by 32-bit offsets
+  // The scan's tiles of 64 rows are addressed by 32-bit offsets.  Over few keys
+  // its two dependent launches per bit cost more than rebuilding the residuals
+  // (8 x 4096 keys, scan against rebuild: L = 32 474 and 457 us, L = 64 1155 and
+  // 1081, L = 128 3894 and 2918; 8 x 8192, L = 64: 1295 and 1675).
+  scan = scan && a.sK_n < (1 << 24) && (int64_t)a.B * a.Hkv * a.N > kScanMinKeys;
   if (scan) launch_build_scan(a, lay);
   switch (a.L) {
     case 32: launch_build_W<1>(a, lay, scan); break;

@@ -662,13 +662,17 @@ __global__ __launch_bounds__(kSolveThreads) void build_solve_kernel(
         two_sum(S, sh[x][d], S, e);
         lo2 += e + sl[x][d];
       }
-      S += lo2;
+      two_sum(S, lo2, S, e);
       const double NE = sqrt(dN * (v_e + 0x1p-36 * v_e0));
       // levels of the tree (one spare) above those whose sums are exact
       const double M = (v_kx + v_aa) * (1.0 + 0x1p-20), top = 0x1p53 * v_qu;
       int levels = 34 - __clz(N);
       for (double x = M; levels > 0 && 2.0 * x < top; x *= 2.0) --levels;
-      const double B = kEps * 1.02 * (v_rs + levels * NE + v_ch * sqrt(dN * v_e0)) + 0x1p-51 * fabs(S);
+      // Where nothing rounds at all both sides hold the same number, which over
+      // short columns often lies halfway between two floats.
+      const bool exact = levels == 0 && v_rs == 0.0 && v_ch == 0.0 && e == 0.0;
+      const double B =
+          exact ? 0.0 : kEps * 1.02 * (v_rs + levels * NE + v_ch * sqrt(dN * v_e0)) + 0x1p-51 * fabs(S);
       const float pl = (float)((S - B) / dN), ph = (float)((S + B) / dN);
       p_s[d] = (double)pl;
       if (!(__float_as_uint(pl) == __float_as_uint(ph) && fabsf(pl) < 3e38f)) redo[atomicAdd(&nredo, 1)] = d;

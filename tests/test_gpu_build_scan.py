@@ -80,8 +80,9 @@ def directions(L, seed=1):
 # one key; one short, one whole, one whole and a bit 64-key tile; a 128-key
 # chunk and a bit; a wavefront's and a workgroup's share and a bit; more than
 # one block per wavefront
-@pytest.mark.parametrize("L,N,B,H", [(32, 1, 1, 1), (64, 63, 1, 2), (64, 64, 2, 1), (128, 65, 1, 2), (32, 129, 1, 3),
-                                     (64, 257, 1, 1), (128, 1025, 2, 2), (64, 40961, 1, 8)])
+# (more than 40960 keys in all, below which the rebuilding passes run anyway)
+@pytest.mark.parametrize("L,N,B,H", [(32, 1, 8, 5200), (64, 63, 8, 96), (64, 64, 8, 96), (128, 65, 8, 96),
+                                     (32, 129, 8, 48), (64, 257, 8, 24), (128, 1025, 8, 8), (64, 40961, 1, 8)])
 def test_sizes(L, N, B, H):
     print(f"[build scan] L={L} N={N} B={B} H={H}", flush=True)
     assert_same(both(keys(N, B, H, seed=N), directions(L), N, codes_stride_rows=3))
@@ -96,7 +97,7 @@ FORMS = ["zero_columns", "negative_zero_columns", "cancelling", "tiny_and_huge",
 def test_forms(form, L):
     N = 640 if form != "strided" else 700
     print(f"[build scan] {form} L={L}", flush=True)
-    K = keys(N, seed=L)
+    K = keys(N, H=72, seed=L)
     if form == "zero_columns":  # heads of 64 padded to 128: those columns of P are zero
         K[..., 64:] = 0
     elif form == "negative_zero_columns":
@@ -121,7 +122,7 @@ def test_forms(form, L):
         K[0, 0, 17, 3] = float("inf")
         K[0, 1, 100, 77] = float("nan")
     elif form == "strided":  # rows of 136 elements, heads interleaved
-        K = torch.zeros(1, N, 2, 136, dtype=torch.bfloat16, device=DEV).transpose(1, 2)[..., :128].copy_(K)
+        K = torch.zeros(1, N, 72, 136, dtype=torch.bfloat16, device=DEV).transpose(1, 2)[..., :128].copy_(K)
     assert_same(both(K, directions(L), N if form != "strided" else N - 57))
 
 
@@ -131,6 +132,6 @@ def test_many_uncertified_columns():
     in the reference order."""
     N, L = 2048, 64
     g = torch.Generator(device=DEV).manual_seed(3)
-    K = torch.randint(-4, 5, (1, 2, N, 128), generator=g, device=DEV).to(torch.bfloat16)
+    K = torch.randint(-4, 5, (1, 24, N, 128), generator=g, device=DEV).to(torch.bfloat16)
     K[:, :, ::2] = -K[:, :, 1::2]
     assert_same(both(K, directions(L), N))
