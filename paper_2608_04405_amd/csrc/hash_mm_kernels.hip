@@ -614,6 +614,9 @@ __global__ __launch_bounds__(hm_threads<L>(), 2) void hash_mm_kernel(const uint1
     if (many) {
       nfrag += hm_reference_tile<L>(Kb, sK_n, base, key_end, sh.Ps, codes + b * sC_b + h * sC_h);
       nfall += (unsigned int)min(64, key_end - base) * L;
+      // (the loop over the blocks may have been left before it loaded these)
+      if constexpr (hm_parts<L>())
+        if (base + NWV * 64 < key_end) load_keys(base + NWV * 64);
       continue;
     }
     nfrag += tfrag, nfall += tfall;

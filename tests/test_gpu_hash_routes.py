@@ -55,7 +55,7 @@ def inputs(N, L, B=1, H=2, seed=0):
 
 
 # one key, a tile and its edges, a 256-key workgroup of the norms and its edges,
-# a wavefront's second tile
+# several workgroups (each wavefront decides one tile here: second_tiles below)
 @pytest.mark.parametrize("L,N", [(32, 1), (64, 63), (128, 65), (64, 256), (128, 257), (32, 255), (64, 1500)])
 def test_sizes(L, N):
     print(f"[hash routes] L={L} N={N}", flush=True)
@@ -100,3 +100,32 @@ def test_forms(form, L):
     elif form == "shared":
         P = P[0, 0].contiguous()
     check(K, P, N - 13 if form == "strided" else N)
+
+
+# Calls of more than 524288 keys give every wavefront a second tile, whose keys
+# are loaded while the first is decided: a workgroup covers 512 keys at L = 32
+# (256 at a time) and 1024 above (512 at a time).  Here the last workgroup's
+# first wavefront goes from a whole tile to one of 10 keys.
+SECOND = [(32, 4096 + 256 + 10), (64, 4096 + 512 + 10), (128, 4096 + 512 + 10)]
+
+
+@pytest.mark.parametrize("L,N", SECOND)
+@pytest.mark.parametrize("form", ["plain", "zero_tiles", "few_zero_keys", "late_zeros"])
+def test_second_tiles(form, L, N):
+    """A whole tile decided in the reference arithmetic (zero keys) must leave
+    the keys of the wavefront's next tile loaded, whichever block of bits it was
+    found in."""
+    print(f"[hash routes] second tiles {form} L={L} N={N}", flush=True)
+    K, P = inputs(N, L, B=16, H=8, seed=11)
+    if form == "zero_tiles":
+        K[:, ::2, 4096:4160] = 0  # before the 10-key tail
+        K[:, :, 1024:1088] = 0    # before an ordinary tile
+        K[:, 1::4, :2048] = 0     # half of a head, as left padding
+    elif form == "few_zero_keys":  # stays with single decisions
+        K[:, :, 4096:4116] = 0
+    elif form == "late_zeros":  # residuals reach 0 after the first block of bits
+        P[:, :, 16:, ::2] = -P[:, :, 16:, 1::2]
+        P[:, :, :16] = 0
+        P[:, :, 0] = 1.0
+        K[:, :, 4096:4160] = 1.0
+    check(K, P, N)
