@@ -408,7 +408,8 @@ __global__ __launch_bounds__(hm_threads<L>(), 2) void hash_mm_kernel(const uint1
     uint32_t cw[W];
 #pragma unroll
     for (int w = 0; w < W; ++w) cw[w] = 0u;
-    unsigned int tfrag = valid && nk < 3.4e38f ? sh.nzero : 0u, tfall = 0;
+    // (the zero rows, where they pass as certain: recomputed ones count themselves)
+    unsigned int tfrag = valid && nkb < 3.4e38f ? sh.nzero : 0u, tfall = 0;
     bool many = false;
 
 #pragma unroll

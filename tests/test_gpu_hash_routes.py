@@ -129,3 +129,21 @@ def test_second_tiles(form, L, N):
         P[:, :, 0] = 1.0
         K[:, :, 4096:4160] = 1.0
     check(K, P, N)
+
+
+@pytest.mark.parametrize("L", [32, 64, 128])
+@pytest.mark.parametrize("N", [20, 64, 84])
+@pytest.mark.parametrize("other", ["infinite", "huge", "plain"])
+def test_zero_rows_beside(other, N, L):
+    """Zero rows of P are counted as fragile once per key, also where another
+    row takes the bounds out of range and single decisions are recomputed (at
+    most 24 keys of a tile)."""
+    print(f"[hash routes] zero rows beside {other} rows N={N} L={L}", flush=True)
+    K, P = inputs(N, L, seed=5)
+    P[:, :, 3] = 0
+    P[:, 1, 20:25] = 0
+    if other == "infinite":
+        P[:, :, 9, 4] = float("inf")
+    elif other == "huge":
+        P[:, :, 9] *= 1e32
+    check(K, P, N)
