@@ -27,8 +27,9 @@
 // (E' = E - 2 p s + N p^2) and bounds sum_j |R_jd| by sqrt(N E_d).  When
 // (float)((s - B) / N) and (float)((s + B) / N) are the same bits, that is
 // P[i][d]; otherwise (about one (b, h) and bit in several hundred) the
-// column's tree is summed in the reference order.  Zero columns, non-finite
-// keys and exactly cancelling sums never certify and take the exact route.
+// column's tree is summed in the reference order.  Columns whose sums are exact
+// certify with B = 0.  Columns with a non-finite key, zero columns with a -0 in
+// them and vanished columns whose sum may be -0 always take the exact route.
 
 #pragma clang fp contract(off)
 
@@ -675,10 +676,14 @@ __global__ __launch_bounds__(kSolveThreads) void build_solve_kernel(
           exact ? 0.0 : kEps * 1.02 * (v_rs + levels * NE + v_ch * sqrt(dN * v_e0)) + 0x1p-51 * fabs(S);
       const float pl = (float)((S - B) / dN), ph = (float)((S + B) / dN);
       p_s[d] = (double)pl;
-      if (!(__float_as_uint(pl) == __float_as_uint(ph) && fabsf(pl) < 3e38f)) redo[atomicAdd(&nredo, 1)] = d;
-      // an all-zero column sums to +0 unless every term is -0: no key with
-      // u = +1, and no padding in the last chunk
-      else if (v_e0 == 0.0 && n_s[bit] == 0 && N % kBuildChunk == 0) p_s[d] = -0.0;
+      // The residuals of an all-zero column are all +0, and those of another
+      // column may have become so exactly: their sum is +0 unless every term is
+      // -0, that is no key has u = +1 and the last chunk no padding.
+      const bool all_negative = n_s[bit] == 0 && N % kBuildChunk == 0;
+      if (!(__float_as_uint(pl) == __float_as_uint(ph) && fabsf(pl) < 3e38f) ||
+          (all_negative && pl == 0.f && v_e0 != 0.0))
+        redo[atomicAdd(&nredo, 1)] = d;
+      else if (all_negative && v_e0 == 0.0) p_s[d] = -0.0;
     }
     __syncthreads();
     const int nr = nredo;

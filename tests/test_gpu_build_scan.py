@@ -135,3 +135,22 @@ def test_many_uncertified_columns():
     K = torch.randint(-4, 5, (1, 24, N, 128), generator=g, device=DEV).to(torch.bfloat16)
     K[:, :, ::2] = -K[:, :, 1::2]
     assert_same(both(K, directions(L), N))
+
+
+@pytest.mark.parametrize("L", [32, 64, 128])
+def test_sign_of_a_vanished_column(L):
+    """A column whose residual has become exactly zero sums to -0 where every
+    term is -0: all u = -1 and no padding row (N a multiple of 128)."""
+    N = 640
+    K = torch.zeros(1, 72, N, 128, dtype=torch.bfloat16, device=DEV)
+    K[..., 0] = 1.0
+    K[:, :, 1::2, 0] = -1.0
+    K[..., 1] = -1.0
+    K[:, 36:, :, 2:] = keys(N, H=36, seed=3)[..., 2:]
+    G = directions(L)
+    G[0], G[1] = 0, 0
+    G[0, 0], G[1, 1] = 1.0, 1.0
+    res = both(K, G, N)
+    assert bool((res[1][0][:, :36, 1, 0].view(torch.int32) == -2 ** 31).all())  # the case arises
+    assert_same(res)
+    assert_same(both(K, G, N - 1))
