@@ -43,3 +43,16 @@ def test_segments(N, m, values):
         want = expected(e[0, h], m)
         assert np.array_equal(got[0, h].cpu().numpy(), want)
         assert np.array_equal(got2[0, h].cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("N,m", [(9000, 7), (12, 3)])
+def test_many_rows(N, m):
+    """More (b, h) than a grid's y dimension takes (65536)."""
+    B, H = 8193, 8
+    print(f"[select tiles] {B} x {H} rows N={N} m={m}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(N)
+    e = torch.rand(B, 1, N, generator=g, device=DEV)
+    t = e.expand(B, H, N)  # head stride 0
+    got = bpc.select_hard(t, m)
+    want = e.sort(dim=-1, descending=True, stable=True).indices[..., :m].sort(-1).values.int()
+    assert torch.equal(got, want.expand(B, H, m))
