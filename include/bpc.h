@@ -354,8 +354,8 @@ int bpc_decode_attention_per_head(const uint16_t* q,
  * serr_out  [B, Hkv, m] int32, contiguous: the selected key indices in
  *           ascending order (written)
  * Both pointers 4-byte aligned.  No workspace; one kernel launch (one
- * workgroup per (b, KV head); beyond 16384 errors, or m > 4096, it makes four
- * passes over its N errors).
+ * workgroup per (b, KV head); up to 6144 and beyond 16384 errors, or m > 4096,
+ * it makes four passes over its N errors).
  *
  * bpc_select_hard_ws is the same selection with bpc_select_hard_workspace_bytes
  * bytes of workspace (4-byte aligned; its contents on entry do not matter; 0

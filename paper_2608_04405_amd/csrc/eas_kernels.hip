@@ -119,6 +119,11 @@ __global__ __launch_bounds__(kHardThreads) void select_hard_kernel(const float* 
 constexpr int kTileRounds = 16;
 constexpr int kTileKeys = kTileRounds * kHardThreads;
 constexpr int kTileMost = kTileKeys / 4;  // largest m: every level then keeps at most a quarter
+// Up to here the one-workgroup kernel's loops are shorter than the segment
+// kernel's 16 rounds (one against the other, 8 heads: 100 errors 6.1 and 12.1 us,
+// 1000 6.7 and 12.4, 4096 9.3 and 12.7, 6000 11.8 and 12.9, 8192 14.8 and 13.3;
+// 1024 heads x 4096 25 and 32, x 8192 40 and 34).
+constexpr int kTileLeast = 6144;
 
 struct TileSource {
   const uint32_t* key;    // floats' bits, or order keys where idx is given
@@ -252,7 +257,7 @@ hipError_t launch_select_hard(const float* err, int64_t sE_b, int64_t sE_h, int 
   const size_t BH = (size_t)B * Hkv;
   // one workgroup per segment in grid x, which takes 2^32 threads
   const size_t wgs = BH * ((N + tile_segment(N) - 1) / tile_segment(N));
-  if (m > 0 && m <= kTileMost && (N <= kTileKeys || ws) && wgs < (1ull << 32) / kHardThreads) {
+  if (m > 0 && m <= kTileMost && N > kTileLeast && (N <= kTileKeys || ws) && wgs < (1ull << 32) / kHardThreads) {
     TileSource src{reinterpret_cast<const uint32_t*>(err), sE_b, sE_h, nullptr, N};
     uint32_t* list = static_cast<uint32_t*>(ws);
     while (src.n > kTileKeys) {

@@ -17,9 +17,10 @@ def expected(e, m):
     return np.sort(np.lexsort((np.arange(len(e)), -key))[:m]).astype(np.int32)
 
 
-# one segment exactly and one key more; m of a whole small input; the largest m
-# of the segments and the first beyond; three levels
-@pytest.mark.parametrize("N,m", [(16384, 1), (16384, 4096), (1000, 1000), (16385, 66), (16385, 4096), (16385, 4097),
+# one segment exactly and one key more; m of a whole small input; the last length
+# of the one-workgroup kernel and the first of a segment; the largest m of the
+# segments and the first beyond; three levels
+@pytest.mark.parametrize("N,m", [(16384, 1), (16384, 4096), (1000, 1000), (6144, 61), (6145, 61), (7000, 1), (16385, 66), (16385, 4096), (16385, 4097),
                                  (40000, 800), (140001, 4096), (600000, 3000), (65536, 1)])
 @pytest.mark.parametrize("values", ["norms", "ties", "wide"])
 def test_segments(N, m, values):
