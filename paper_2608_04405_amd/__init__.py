@@ -34,6 +34,7 @@ __all__ = [
     "decode_per_head_workspace_bytes",
     "dense_attention",
     "select_hard",
+    "select_hard_workspace_bytes",
     "DECODE_STAGES",
     "DECODE_STAGE_NAMES",
     "version",
@@ -544,11 +545,21 @@ def decode_attention_per_head(q: torch.Tensor, K: torch.Tensor, V: torch.Tensor,
     return out
 
 
+def select_hard_workspace_bytes(B: int, Hkv: int, N: int, m: int) -> int:
+    """Bytes of workspace with which select_hard reads its errors only once
+    (0 where that would not help)."""
+    return int(_lib.bpc_select_hard_workspace_bytes(B, Hkv, N, m))
+
+
 def select_hard(err: torch.Tensor, m: int, N: Optional[int] = None, *, serr_out: Optional[torch.Tensor] = None,
-                stream=None) -> torch.Tensor:
+                workspace: Optional[torch.Tensor] = None, stream=None) -> torch.Tensor:
     """The error-aware safeguard's hard-to-hash set: per (b, KV head), the m
     keys with the largest reconstruction errors (err [B, Hkv, >=N] fp32, as
-    written by build_hash / hash_keys), ascending; returns [B, Hkv, m] int32."""
+    written by build_hash / hash_keys), ascending; returns [B, Hkv, m] int32.
+    `workspace` (uint8, select_hard_workspace_bytes) is allocated here where it
+    helps and is not given; not while a stream is being captured, whose graph
+    would outlive it: there the selection without a workspace runs, the same
+    set in more passes."""
     _need(err, "err", torch.float32, 3)
     B, Hkv, Ncap = err.shape
     N = Ncap if N is None else N
@@ -557,19 +568,21 @@ def select_hard(err: torch.Tensor, m: int, N: Optional[int] = None, *, serr_out:
     if not 0 <= m <= N:
         raise ValueError(f"m={m} must satisfy 0 <= m <= N={N}")
     _exact_out(serr_out, "serr_out", torch.int32, (B, Hkv, m))
-    _on_gpu(err, serr_out)
+    _on_gpu(err, serr_out, workspace)
     if serr_out is None:
         serr_out = torch.empty(B, Hkv, m, dtype=torch.int32, device=err.device)
-    size = int(_lib.bpc_select_hard_workspace_bytes(B, Hkv, N, m))
-    ws = None
-    if size:
+    size = select_hard_workspace_bytes(B, Hkv, N, m)
+    if size and workspace is None and (stream is None or isinstance(stream, torch.cuda.Stream)):
         # allocated on the stream that uses it, so that its memory is not
         # reused elsewhere while the kernels run
         with torch.cuda.stream(stream) if stream is not None else contextlib.nullcontext():
-            ws = torch.empty(size, dtype=torch.uint8, device=err.device)
-    _check(_lib.bpc_select_hard_ws(_ptr(err), err.stride(0), err.stride(1), B, Hkv, N, m, _ptr(serr_out),
-                                   _ptr(ws), size, _stream(stream)),
-           "bpc_select_hard")
+            if not torch.cuda.is_current_stream_capturing():
+                workspace = torch.empty(size, dtype=torch.uint8, device=err.device)
+    args = (_ptr(err), err.stride(0), err.stride(1), B, Hkv, N, m, _ptr(serr_out))
+    if size and workspace is not None:
+        _check(_lib.bpc_select_hard_ws(*args, _ptr(workspace), workspace.numel(), _stream(stream)), "bpc_select_hard")
+    else:
+        _check(_lib.bpc_select_hard(*args, _stream(stream)), "bpc_select_hard")
     return serr_out
 
 

@@ -57,3 +57,45 @@ def test_many_rows(N, m):
     got = bpc.select_hard(t, m)
     want = e.sort(dim=-1, descending=True, stable=True).indices[..., :m].sort(-1).values.int()
     assert torch.equal(got, want.expand(B, H, m))
+
+
+def test_workspace_and_capture():
+    """A given workspace is used; a captured call allocates nothing (a graph
+    would outlive the allocation); any stream object with a handle is taken."""
+    N, m = 40000, 800
+    e = torch.rand(2, 2, N, generator=torch.Generator(device=DEV).manual_seed(1), device=DEV)
+    want = torch.from_numpy(np.stack([expected(r, m) for r in e.cpu().numpy().reshape(4, N)])).reshape(2, 2, m).to(DEV)
+    size = bpc.select_hard_workspace_bytes(2, 2, N, m)
+    assert size > 0 and bpc.select_hard_workspace_bytes(2, 2, 4096, 40) == 0
+    ws = torch.randint(0, 256, (size,), dtype=torch.uint8, device=DEV)
+    out = torch.empty(2, 2, m, dtype=torch.int32, device=DEV)
+
+    def allocations():
+        return torch.cuda.memory_stats()["allocation.all.allocated"]
+
+    before = allocations()
+    bpc.select_hard(e, m, serr_out=out, workspace=ws)
+    assert allocations() == before
+    assert torch.equal(out, want)
+    with pytest.raises(bpc.BPCError):
+        bpc.select_hard(e, m, serr_out=out, workspace=ws[: size // 2])
+
+    class Handle:
+        cuda_stream = torch.cuda.current_stream().cuda_stream
+
+    assert torch.equal(bpc.select_hard(e, m, stream=Handle()), want)
+
+    side = torch.cuda.Stream()
+    for given in (None, ws):
+        with torch.cuda.stream(side):
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph, stream=side):
+                before = allocations()
+                bpc.select_hard(e, m, serr_out=out, workspace=given)
+                assert allocations() == before
+        for _ in range(3):
+            out.fill_(-1)
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(out, want)
