@@ -175,9 +175,10 @@ int bpc_build_hash(const uint16_t* K, int64_t sK_b, int64_t sK_h, int64_t sK_n,
  * codes_out  [B, Hkv, >=N, W] uint32, strides sC_b, sC_h (written)
  * err_out    [B, Hkv, N] fp32 contiguous ||r_final|| (or NULL)
  * fragile_out  device uint64 accumulator (or NULL), as above.
- * No workspace; one kernel launch, and one more for err_out.  The codes come
- * from the kernel of bpc_hash_keys_mm (below: certified signs, every other
- * decision in the arithmetic above), the norms from the residual itself.
+ * No workspace; over many keys two kernel launches, the kernel of
+ * bpc_hash_keys_mm (below: certified signs, every other decision in the
+ * arithmetic above) and, for err_out, one that forms the residual; over few
+ * keys one launch in the arithmetic above throughout.
  */
 int bpc_hash_keys(const uint16_t* K, int64_t sK_b, int64_t sK_h, int64_t sK_n,
                   int B, int Hkv, int N, int D, int L,

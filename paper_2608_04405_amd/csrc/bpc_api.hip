@@ -244,11 +244,16 @@ int bpc_hash_keys(const uint16_t* K, int64_t sK_b, int64_t sK_h, int64_t sK_n, i
   if ((st = check_proj(P, sP_b, sP_h))) return st;
   if ((st = check_codes("codes_out", codes_out, sC_b, sC_h, L / 32))) return st;
   if ((st = check_opt_aligned("err_out", err_out))) return st;
-  hipError_t e = launch_hash_mm(K, sK_b, sK_h, sK_n, B, Hkv, N, L, P, sP_b, sP_h, codes_out, sC_b, sC_h, fragile_out,
-                                nullptr, static_cast<hipStream_t>(stream));
-  if (e == hipSuccess && err_out)
-    e = launch_norm(K, sK_b, sK_h, sK_n, B, Hkv, N, L, P, sP_b, sP_h, codes_out, sC_b, sC_h, err_out,
-                    static_cast<hipStream_t>(stream));
+  const hipStream_t hs = static_cast<hipStream_t>(stream);
+  hipError_t e;
+  if (hash_few_keys((int64_t)B * Hkv, N, L, err_out != nullptr)) {
+    e = launch_hash(K, sK_b, sK_h, sK_n, B, Hkv, N, L, P, sP_b, sP_h, codes_out, sC_b, sC_h, err_out, fragile_out, hs);
+  } else {
+    e = launch_hash_mm(K, sK_b, sK_h, sK_n, B, Hkv, N, L, P, sP_b, sP_h, codes_out, sC_b, sC_h, fragile_out, nullptr,
+                       hs);
+    if (e == hipSuccess && err_out)
+      e = launch_norm(K, sK_b, sK_h, sK_n, B, Hkv, N, L, P, sP_b, sP_h, codes_out, sC_b, sC_h, err_out, hs);
+  }
   if (e != hipSuccess) return hip_fail(e, "bpc_hash_keys launch");
   return BPC_OK;
 }
@@ -294,8 +299,8 @@ int bpc_append_kv(const uint16_t* k_new, int64_t sKn_b, int64_t sKn_h, int64_t s
   cp.Kc = K + (int64_t)pos * sK_n, cp.sKc_b = sK_b, cp.sKc_h = sK_h, cp.sKc_n = sK_n;
   cp.Vn = v_new, cp.sVn_b = sVn_b, cp.sVn_h = sVn_h, cp.sVn_n = sVn_t;
   cp.Vc = V + (int64_t)pos * sV_n, cp.sVc_b = sV_b, cp.sVc_h = sV_h, cp.sVc_n = sV_n;
-  hipError_t e = launch_append(k_new, sKn_b, sKn_h, sKn_t, B, Hkv, T, L, P, sP_b, sP_h,
-                               codes + (int64_t)pos * (L / 32), sC_b, sC_h, err_out, fragile_out, static_cast<hipStream_t>(stream), &cp);
+  hipError_t e = launch_hash(k_new, sKn_b, sKn_h, sKn_t, B, Hkv, T, L, P, sP_b, sP_h, codes + (int64_t)pos * (L / 32),
+                             sC_b, sC_h, err_out, fragile_out, static_cast<hipStream_t>(stream), &cp);
   if (e != hipSuccess) return hip_fail(e, "bpc_append_kv launch");
   return BPC_OK;
 }

@@ -191,15 +191,24 @@ struct AppendCopy {
   int64_t sVc_b, sVc_h, sVc_n;
 };
 
-// hash N keys into `codes` in the fixed-order arithmetic and copy them and
-// their value rows
-hipError_t launch_append(const uint16_t* K, int64_t sK_b, int64_t sK_h, int64_t sK_n, int B, int Hkv,
-                       int N, int L, const float* P, int64_t sP_b, int64_t sP_h, uint32_t* codes,
-                       int64_t sC_b, int64_t sC_h, float* err, unsigned long long* fragile,
-                       hipStream_t stream, const AppendCopy* append);
+// Algorithm 2 in the fixed-order arithmetic; with `append` the keys and their
+// value rows are copied too
+hipError_t launch_hash(const uint16_t* K, int64_t sK_b, int64_t sK_h, int64_t sK_n, int B, int Hkv, int N, int L,
+                       const float* P, int64_t sP_b, int64_t sP_h, uint32_t* codes, int64_t sC_b, int64_t sC_h,
+                       float* err, unsigned long long* fragile, hipStream_t stream,
+                       const AppendCopy* append = nullptr);
+
+// Whether bpc_hash_keys runs launch_hash, one launch whose time is that of its
+// chain of bits while the chip is not full, rather than the matrix-core kernel
+// (and launch_norm): with norms while its workgroups of 64 keys are at most two
+// per compute unit, or a head has one of them (fixed-order against the other,
+// L = 64: 8 x 512 keys 40 and 62 us, 8 x 4096 58 and 66, 8 x 6000 79 and 67,
+// 1024 x 64 110 and 185, 1024 x 128 197 and 199); without norms only at L = 128
+// (8 x 1024 70 and 78 us, 8 x 4096 113 and 79, 8 x 128 70 and 59).
+bool hash_few_keys(int64_t BH, int N, int L, bool norms);
 
 // Algorithm 2 with the projections on the matrix cores and certified signs
-// (codes and fragile count of the fixed-order arithmetic; no residual norms).
+// (codes and fragile count identical to launch_hash; no residual norms).
 hipError_t launch_hash_mm(const uint16_t* K, int64_t sK_b, int64_t sK_h, int64_t sK_n, int B, int Hkv, int N, int L,
                           const float* P, int64_t sP_b, int64_t sP_h, uint32_t* codes, int64_t sC_b, int64_t sC_h,
                           unsigned long long* fragile, unsigned long long* fallbacks, hipStream_t stream);

@@ -429,7 +429,8 @@ hipError_t launch_norm(const uint16_t* K, int64_t sK_b, int64_t sK_h, int64_t sK
 }
 
 // ============================================================================
-// Algorithm 2 for decode-time append.  Four lanes per key: lane q of a quad holds the fp64
+// Algorithm 2 in the reference arithmetic, for decode-time append and for few
+// keys.  Four lanes per key: lane q of a quad holds the fp64
 // residual of coordinates [32q, 32q + 32) in registers, so each bit's dot
 // product is four sequential block sums combined across the quad as
 // ((b0 + b1) + (b2 + b3)) -- the fixed order -- and the residual update
@@ -437,9 +438,10 @@ hipError_t launch_norm(const uint16_t* K, int64_t sK_b, int64_t sK_h, int64_t sK
 // workgroup (padded rows avoid bank conflicts between the four blocks).
 // ============================================================================
 
-// Each key row of K (the new keys) is also stored into the cache rows cp.Kc,
-// and the matching value rows cp.Vn into cp.Vc; the four lanes of a key each
-// move a quarter of both rows.
+// With a cache copy (cp.Kc non-null), decode-time append: each key row of K
+// (the new keys) is also stored into the cache rows cp.Kc, and the matching
+// value rows cp.Vn into cp.Vc; the four lanes of a key each move a quarter
+// of both rows.
 template <int L>
 __global__ __launch_bounds__(256) void hash_kernel(const uint16_t* __restrict__ K, int64_t sK_b, int64_t sK_h,
                                                    int64_t sK_n, int Hkv, int N, const float* __restrict__ P,
@@ -476,7 +478,7 @@ __global__ __launch_bounds__(256) void hash_kernel(const uint16_t* __restrict__ 
       for (int e = 0; e < 8; ++e)
         r[8 * c + e] = bf16_to_f64((uint16_t)((e & 1) ? (w[e >> 1] >> 16) : (w[e >> 1] & 0xFFFFu)));
     }
-    {
+    if (cp.Kc) {
       uint16_t* kc = cp.Kc + b * cp.sKc_b + h * cp.sKc_h + (int64_t)key * cp.sKc_n + 32 * qd;
       const uint16_t* vn = cp.Vn + b * cp.sVn_b + h * cp.sVn_h + (int64_t)key * cp.sVn_n + 32 * qd;
       uint16_t* vc = cp.Vc + b * cp.sVc_b + h * cp.sVc_h + (int64_t)key * cp.sVc_n + 32 * qd;
@@ -650,46 +652,42 @@ __global__ __launch_bounds__(64) void append_kernel(const uint16_t* __restrict__
 
 // New keys per (b, h) up to which each gets a wavefront of its own; beyond,
 // sixteen keys per wavefront issue less in all (measured at 16 x 8 heads).
-constexpr int kAppendWaveKeys = 32;
+static bool append_by_wave(int64_t, int N) { return N <= 32; }
 
-hipError_t launch_append(const uint16_t* K, int64_t sK_b, int64_t sK_h, int64_t sK_n, int B, int Hkv, int N, int L,
+template <int L>
+static hipError_t launch_hash_L(const uint16_t* K, int64_t sK_b, int64_t sK_h, int64_t sK_n, int B, int Hkv, int N,
+                                const float* P, int64_t sP_b, int64_t sP_h, uint32_t* codes, int64_t sC_b,
+                                int64_t sC_h, float* err, unsigned long long* fragile, hipStream_t stream,
+                                const AppendCopy* append) {
+  if (append && append_by_wave((int64_t)B * Hkv, N))
+    append_kernel<L><<<dim3(N, B * Hkv), 64, 0, stream>>>(K, sK_b, sK_h, sK_n, Hkv, N, P, sP_b, sP_h, codes, sC_b,
+                                                          sC_h, err, fragile, *append);
+  else
+    hash_kernel<L><<<dim3((N + 63) / 64, B * Hkv), 256, 0, stream>>>(K, sK_b, sK_h, sK_n, Hkv, N, P, sP_b, sP_h, codes,
+                                                                     sC_b, sC_h, err, fragile,
+                                                                     append ? *append : AppendCopy{});
+  return hipGetLastError();
+}
+
+hipError_t launch_hash(const uint16_t* K, int64_t sK_b, int64_t sK_h, int64_t sK_n, int B, int Hkv, int N, int L,
                        const float* P, int64_t sP_b, int64_t sP_h, uint32_t* codes, int64_t sC_b, int64_t sC_h,
                        float* err, unsigned long long* fragile, hipStream_t stream, const AppendCopy* append) {
-  const dim3 grid((N + 63) / 64, B * Hkv);
-  const AppendCopy cp = *append;
-  if (N <= kAppendWaveKeys) {
-    const dim3 waves(N, B * Hkv);
-    switch (L) {
-      case 32:
-        append_kernel<32><<<waves, 64, 0, stream>>>(K, sK_b, sK_h, sK_n, Hkv, N, P, sP_b, sP_h, codes, sC_b, sC_h, err,
-                                                    fragile, cp);
-        break;
-      case 64:
-        append_kernel<64><<<waves, 64, 0, stream>>>(K, sK_b, sK_h, sK_n, Hkv, N, P, sP_b, sP_h, codes, sC_b, sC_h, err,
-                                                    fragile, cp);
-        break;
-      default:
-        append_kernel<128><<<waves, 64, 0, stream>>>(K, sK_b, sK_h, sK_n, Hkv, N, P, sP_b, sP_h, codes, sC_b, sC_h,
-                                                     err, fragile, cp);
-        break;
-    }
-    return hipGetLastError();
-  }
   switch (L) {
     case 32:
-      hash_kernel<32><<<grid, 256, 0, stream>>>(K, sK_b, sK_h, sK_n, Hkv, N, P, sP_b, sP_h, codes, sC_b, sC_h, err,
-                                                fragile, cp);
-      break;
+      return launch_hash_L<32>(K, sK_b, sK_h, sK_n, B, Hkv, N, P, sP_b, sP_h, codes, sC_b, sC_h, err, fragile, stream,
+                               append);
     case 64:
-      hash_kernel<64><<<grid, 256, 0, stream>>>(K, sK_b, sK_h, sK_n, Hkv, N, P, sP_b, sP_h, codes, sC_b, sC_h, err,
-                                                fragile, cp);
-      break;
+      return launch_hash_L<64>(K, sK_b, sK_h, sK_n, B, Hkv, N, P, sP_b, sP_h, codes, sC_b, sC_h, err, fragile, stream,
+                               append);
     default:
-      hash_kernel<128><<<grid, 256, 0, stream>>>(K, sK_b, sK_h, sK_n, Hkv, N, P, sP_b, sP_h, codes, sC_b, sC_h,
-                                                 err, fragile, cp);
-      break;
+      return launch_hash_L<128>(K, sK_b, sK_h, sK_n, B, Hkv, N, P, sP_b, sP_h, codes, sC_b, sC_h, err, fragile, stream,
+                                append);
   }
-  return hipGetLastError();
+}
+
+bool hash_few_keys(int64_t BH, int N, int L, bool norms) {
+  const int64_t wgs = BH * ((N + 63) / 64);
+  return norms ? wgs <= 512 || N <= 64 : L == 128 && N > 256 && wgs <= 256;
 }
 
 }  // namespace bpc

@@ -1,5 +1,6 @@
-"""hash_keys (codes on the matrix cores with certified signs, residual norms
-apart) and hash_keys_mm against the kernel of decode-time append, which keeps
+"""hash_keys (over many keys: codes on the matrix cores with certified signs,
+residual norms apart; over few, in the reference arithmetic throughout) and
+hash_keys_mm against the kernel of decode-time append, which keeps
 the residual of Algorithm 2 and decides every bit in the reference arithmetic:
 the same codes, norms and fragile counts bit for bit, over the forms in which
 certified decisions are rare.  (The append kernel is checked against the oracle
@@ -56,19 +57,24 @@ def inputs(N, L, B=1, H=2, seed=0):
 
 # one key, a tile and its edges, a 256-key workgroup of the norms and its edges,
 # several workgroups (each wavefront decides one tile here: second_tiles below)
-@pytest.mark.parametrize("L,N", [(32, 1), (64, 63), (128, 65), (64, 256), (128, 257), (32, 255), (64, 1500)])
-def test_sizes(L, N):
-    print(f"[hash routes] L={L} N={N}", flush=True)
-    check(*inputs(N, L, B=2), N)
+# (calls of 8 heads take the reference arithmetic with norms; with more than 512
+# groups of 64 keys, and more than one per head, the norms are apart)
+@pytest.mark.parametrize("L,N,B", [(32, 1, 2), (64, 63, 2), (128, 65, 2), (64, 256, 2), (128, 257, 2), (32, 255, 2),
+                                   (64, 1500, 2), (64, 64, 260), (64, 65, 128), (128, 65, 129), (32, 255, 70),
+                                   (64, 256, 65), (128, 257, 60), (64, 1500, 12)])
+def test_sizes(L, N, B):
+    print(f"[hash routes] L={L} N={N} B={B}", flush=True)
+    check(*inputs(N, L, B=B), N)
 
 
+@pytest.mark.parametrize("B", [1, 60])
 @pytest.mark.parametrize("L", [32, 64, 128])
 @pytest.mark.parametrize("form", ["zero_rows", "zero_projection", "zero_keys", "exact_fit", "few_uncertain", "non_finite",
                                   "huge", "tiny", "strided", "shared"])
-def test_forms(form, L):
-    print(f"[hash routes] {form} L={L}", flush=True)
+def test_forms(form, L, B):
+    print(f"[hash routes] {form} L={L} B={B}", flush=True)
     N = 300
-    K, P = inputs(N, L, seed=7)
+    K, P = inputs(N, L, B=B, seed=7)
     if form == "zero_rows":  # a head whose keys ran out of directions
         P[:, :, L // 2:] = 0
         P[:, :, 3] = 0
@@ -80,7 +86,7 @@ def test_forms(form, L):
         P[:] = 0
         P[:, :, 0, :64] = 1.5
         P[:, :, 1, 64:] = 0.25
-        K = torch.cat([P[:, :, :1, :64].expand(1, 2, N, 64), P[:, :, 1:2, 64:].expand(1, 2, N, 64)], -1)
+        K = torch.cat([P[:, :, :1, :64].expand(B, 2, N, 64), P[:, :, 1:2, 64:].expand(B, 2, N, 64)], -1)
         K = K.to(torch.bfloat16).contiguous()
         P[:, :, 2:] = torch.randn_like(P[:, :, 2:])
         P[:, :, 2:, ::2] = -P[:, :, 2:, 1::2]
@@ -96,7 +102,7 @@ def test_forms(form, L):
     elif form == "tiny":
         K = (K.float() * 2.0 ** -120).to(torch.bfloat16)
     elif form == "strided":
-        K = torch.zeros(1, N, 2, 144, dtype=torch.bfloat16, device=DEV).transpose(1, 2)[..., :128].copy_(K)
+        K = torch.zeros(B, N, 2, 144, dtype=torch.bfloat16, device=DEV).transpose(1, 2)[..., :128].copy_(K)
     elif form == "shared":
         P = P[0, 0].contiguous()
     check(K, P, N - 13 if form == "strided" else N)
