@@ -650,9 +650,13 @@ __global__ __launch_bounds__(64) void append_kernel(const uint16_t* __restrict__
   if (fragile && lane == 0 && nfrag) atomicAdd(fragile, (unsigned long long)nfrag);
 }
 
-// New keys per (b, h) up to which each gets a wavefront of its own; beyond,
-// sixteen keys per wavefront issue less in all (measured at 16 x 8 heads).
-static bool append_by_wave(int64_t, int N) { return N <= 32; }
+// Whether each of N new keys gets a wavefront of its own: up to 16 always; up
+// to 32 while the wavefronts are at most 16 per compute unit (4096 in all).
+// Beyond, sixteen keys per wavefront issue less (wavefront per key against
+// that; L = 64: 32 x 8 heads, T = 16 29.6 and 42.7 us, T = 32 46.4 and 42.2;
+// 16 x 8 heads, T = 32 26 and 40; L = 128: 128 x 8 heads, T = 16 198 and 227,
+// T = 20 243 and 228; 16 x 8 heads, T = 32 55 and 72).
+static bool append_by_wave(int64_t BH, int N) { return N <= 16 || (N <= 32 && BH * N <= 4096); }
 
 template <int L>
 static hipError_t launch_hash_L(const uint16_t* K, int64_t sK_b, int64_t sK_h, int64_t sK_n, int B, int Hkv, int N,

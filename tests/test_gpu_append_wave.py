@@ -62,3 +62,21 @@ def test_chunks(form, L):
                 assert bool(((a == b) | (a.isnan() & b.isnan())).all())
             else:
                 assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+
+
+@pytest.mark.parametrize("L", [32, 64, 128])
+@pytest.mark.parametrize("T,H", [(16, 300), (17, 240), (17, 300), (32, 128), (32, 129)])
+def test_counts(T, H, L):
+    """The number of new keys and heads at which a wavefront per key stops: the
+    same results on either side as with four lanes per key."""
+    print(f"[append wave] T={T} H={H} L={L}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(L + T)
+    k = torch.randn(1, H, 2 * T, 128, generator=g, device=DEV).to(torch.bfloat16)
+    v = torch.randn(1, H, 2 * T, 128, generator=g, device=DEV).to(torch.bfloat16)
+    P = torch.randn(1, H, L, 128, generator=g, device=DEV)
+    wide = lambda x: torch.cat([x, x, x], 2)[:, :, :33].contiguous()  # 33 keys: four lanes per key
+    want = run(wide(k[:, :, :T]), wide(v[:, :, :T]), P, 33)
+    got = run(k[:, :, :T].contiguous(), v[:, :, :T].contiguous(), P, T)
+    for a, b in zip(got[:3], want[:3]):
+        assert torch.equal(a[:, :, 2:2 + T], b[:, :, 2:2 + T])
+    assert torch.equal(got[3], want[3][:, :, :T])
