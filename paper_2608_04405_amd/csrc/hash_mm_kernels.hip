@@ -50,7 +50,7 @@
 // Where more than kHmMany of a tile's 64 keys are uncertain in one block of
 // bits (rank-deficient keys, a P that fits them exactly) the whole tile is
 // decided in the reference arithmetic, four lanes per key; rows of P that are
-// zero need neither.
+// zero, and the first other row for keys that are zero, need neither.
 //
 // What bounds it: vector issue and LDS reads (each block's triangle of
 // corrections, its operands read uniformly from LDS), at two wavefronts per
@@ -222,6 +222,7 @@ struct HmShared {
   float Xs[hm_threads<L>() / 64][64 * kHmXsStride];  // per wavefront: MFMA tile -> one key per lane (also setup scratch)
   double fb[hm_threads<L>() / 64][kHeadDim];  // per wavefront: the products of one reference decision
   unsigned int nzero;                     // zero rows of P
+  unsigned int first;                     // the first row that is not zero (L: none)
   unsigned int nfrag, nfall;
 };
 
@@ -248,7 +249,7 @@ __global__ __launch_bounds__(hm_threads<L>(), 2) void hash_mm_kernel(const uint1
     const int i = e >> 5, c = e & 31;
     *reinterpret_cast<float4*>(&sh.Ps[i * kHmPsStride + 4 * c]) = reinterpret_cast<const float4*>(Pb)[e];
   }
-  if (tid == 0) sh.nfrag = 0, sh.nfall = 0, sh.nzero = 0, sh.emax[0] = 0u, sh.emax[1] = 0u;
+  if (tid == 0) sh.nfrag = 0, sh.nfall = 0, sh.nzero = 0, sh.first = L, sh.emax[0] = 0u, sh.emax[1] = 0u;
   __syncthreads();
   double* Ad = reinterpret_cast<double*>(&sh.Xs[0][0]);  // sum_t |P_td|, [128]
   double* nP = Ad + kHeadDim;                             // |P_t| in fp64, [L]
@@ -330,6 +331,7 @@ __global__ __launch_bounds__(hm_threads<L>(), 2) void hash_mm_kernel(const uint1
       sh.cst[i] = make_float2(0.f, -3e38f);
       atomicAdd(&sh.nzero, 1u);
     } else {
+      atomicMin(&sh.first, (unsigned int)i);
       // (infinite and NaN bounds have the largest bits)
       atomicMax(&sh.emax[0], __float_as_uint(e1) & 0x7FFFFFFFu);
       atomicMax(&sh.emax[1], __float_as_uint(e3) & 0x7FFFFFFFu);
@@ -405,13 +407,33 @@ __global__ __launch_bounds__(hm_threads<L>(), 2) void hash_mm_kernel(const uint1
     const float nkb = fmaf(nk, e1max, e3max) < 1e30f ? nk : __builtin_inff();
     const bool valid = base + lane < key_end;
     const uint16_t* my_row = Kb + (int64_t)(base + lane) * sK_n;
+    // Zero keys (padding): up to the first row of P that is not zero the residual
+    // is zero and a = +0, so that bit is u = +1 and fragile without recomputing;
+    // a^ is +0 there too.  Half of 8 x 131072 keys zero: 108, 169, 465 us at
+    // L = 32, 64, 128, as without zero keys (437, 900, 1845 with their tiles in
+    // the reference arithmetic).  Found from the operands in registers; at L = 128
+    // that costs all keys 3 %, and uncertain keys are looked at again instead.
+    uint32_t zbit = 0xFFFFu;
+    if (hm_parts<L>() && __ballot(ssq == 0.f)) {  // (squares below 2^-149 vanish: the keys themselves decide)
+      uint32_t mine = 0u;
+#pragma unroll
+      for (int tau = 0; tau < 4; ++tau) {
+        uint32_t any = 0u;
+#pragma unroll
+        for (int m = 0; m < 4; ++m) any |= (kv[tau][m].x | kv[tau][m].y) | (kv[tau][m].z | kv[tau][m].w);
+        any |= (uint32_t)__shfl_xor((int)any, 16, 64);
+        any |= (uint32_t)__shfl_xor((int)any, 32, 64);
+        mine = g4 == tau ? any & 0x7FFF7FFFu : mine;
+      }
+      if (valid && mine == 0u && nkb < 3.4e38f) zbit = sh.first;
+    }
     uint32_t cw[W];
 #pragma unroll
     for (int w = 0; w < W; ++w) cw[w] = 0u;
     // (the zero rows, where they pass as certain: recomputed ones count themselves)
     unsigned int tfrag = valid && nkb < 3.4e38f ? sh.nzero : 0u, tfall = 0;
+    if (zbit < (uint32_t)L) ++tfrag;
     bool many = false;
-
 #pragma unroll
     for (int T = 0; T < L / 16; ++T) {
       if (many) break;
@@ -545,11 +567,27 @@ __global__ __launch_bounds__(hm_threads<L>(), 2) void hash_mm_kernel(const uint1
         }
       }
       uint32_t ub = __brev(~neg) >> 16;
-      unc = valid ? __brev(unc) >> 16 : 0u;
+      const uint32_t zm = (zbit >> 4) == (uint32_t)T ? 1u << (zbit & 15u) : 0u;
+      unc = valid ? (__brev(unc) >> 16) & ~zm : 0u;
       uint32_t ovm = 0u, ovv = 0u;
       while (true) {
         unsigned long long todo = __ballot(unc != 0u);
         if (!todo) break;
+        if (!hm_parts<L>() && (int)(sh.first >> 4) == T) {
+          const uint32_t zm = 1u << (sh.first & 15u);
+          const bool may = (unc & zm) && nkb == 0.f;
+          if (__ballot(may)) {
+            uint32_t any = 0u;
+            if (may)
+              for (int q = 0; q < kHeadDim / 8; ++q) {
+                const uint4 v = reinterpret_cast<const uint4*>(my_row)[q];
+                any |= (v.x | v.y) | (v.z | v.w);
+              }
+            if (may && (any & 0x7FFF7FFFu) == 0u) unc &= ~zm, ovm |= zm, ovv |= zm, ++tfrag;
+            todo = __ballot(unc != 0u);
+            if (!todo) break;
+          }
+        }
         many = __popcll(todo) > kHmMany;
         if (many) break;
         bool rerun = false;
@@ -599,7 +637,7 @@ __global__ __launch_bounds__(hm_threads<L>(), 2) void hash_mm_kernel(const uint1
           const bool sure = !valid || fabsf(a) > fmaf(nkb, cb.x, cb.y);
           bool u = a >= 0.f;
           if ((ovm >> i) & 1u) u = (ovv >> i) & 1u;
-          else if (!sure) unc |= 1u << i;
+          else if (!sure) unc |= (1u << i) & ~zm;
           ub |= (u ? 1u : 0u) << i;
           if (i < 15) {
             const float sg = u ? -1.f : 1.f;

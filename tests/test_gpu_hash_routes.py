@@ -116,17 +116,22 @@ SECOND = [(32, 4096 + 256 + 10), (64, 4096 + 512 + 10), (128, 4096 + 512 + 10)]
 
 
 @pytest.mark.parametrize("L,N", SECOND)
-@pytest.mark.parametrize("form", ["plain", "zero_tiles", "few_zero_keys", "late_zeros"])
+@pytest.mark.parametrize("form", ["plain", "zero_tiles", "cancelling_tiles", "few_zero_keys", "late_zeros"])
 def test_second_tiles(form, L, N):
-    """A whole tile decided in the reference arithmetic (zero keys) must leave
-    the keys of the wavefront's next tile loaded, whichever block of bits it was
-    found in."""
+    """A whole tile decided in the reference arithmetic (its keys' products with
+    a row of P cancel) must leave the keys of the wavefront's next tile loaded,
+    whichever block of bits it was found in.  Zero keys need no such tile."""
     print(f"[hash routes] second tiles {form} L={L} N={N}", flush=True)
     K, P = inputs(N, L, B=16, H=8, seed=11)
     if form == "zero_tiles":
         K[:, ::2, 4096:4160] = 0  # before the 10-key tail
         K[:, :, 1024:1088] = 0    # before an ordinary tile
         K[:, 1::4, :2048] = 0     # half of a head, as left padding
+    elif form == "cancelling_tiles":  # a_0 = 0: uncertain in the first block
+        P[:, :, 0, ::2] = -P[:, :, 0, 1::2]
+        K[:, ::2, 4096:4160] = 1.0
+        K[:, :, 1024:1088] = 1.0
+        K[:, 1::4, :2048] = 1.0
     elif form == "few_zero_keys":  # stays with single decisions
         K[:, :, 4096:4116] = 0
     elif form == "late_zeros":  # residuals reach 0 after the first block of bits
@@ -152,4 +157,26 @@ def test_zero_rows_beside(other, N, L):
         P[:, :, 9, 4] = float("inf")
     elif other == "huge":
         P[:, :, 9] *= 1e32
+    check(K, P, N)
+
+
+@pytest.mark.parametrize("L", [32, 64, 128])
+@pytest.mark.parametrize("lead", [0, 1, 17, 31, "all"])
+def test_zero_keys(lead, L):
+    """Zero keys (of either sign), and keys whose squares vanish in fp32, among
+    ordinary ones: up to the first row of P that is not zero, whichever block it
+    lies in, their decisions are exact zeros."""
+    print(f"[hash routes] zero keys after {lead} zero rows L={L}", flush=True)
+    N = 200
+    K, P = inputs(N, L, B=70, seed=3)
+    P[:, :, : L if lead == "all" else lead] = 0
+    K[:, :, 64:128] = 0
+    K[:, :, 64:128:3] = -K[:, :, 64:128:3]
+    K[:, :, 130] = 0
+    K[:, :, 150, :] = 0
+    K[:, :, 150, 7] = 2.0 ** -80  # not zero
+    K[:, :, 64, 9] = 2.0 ** -126
+    check(K, P, N)
+    P[:, 1, L - 1, 5] = float("inf")  # no usable bound
+    check(K[:1], P[:1], 20)
     check(K, P, N)
