@@ -435,7 +435,11 @@ int bpc_decode_attention_per_head(const uint16_t* q, const uint16_t* K, int64_t 
   if ((st = check_code_len(L))) return st;
   if ((st = check_codes("codes", codes, sC_b, sC_h, L / 32))) return st;
   if ((st = check_proj(P, sP_b, sP_h))) return st;
-  const size_t need = bpc_decode_per_head_workspace_bytes(B, Hq, Hkv, N, D, L, k);
+  size_t need = bpc_decode_per_head_workspace_bytes(B, Hq, Hkv, N, D, L, k);
+  if (need) {  // a workspace sized for larger slices runs on those, as in decode_impl
+    const size_t larger = decode_layout(B * Hkv, Hq / Hkv, Hq / Hkv, N, L, k, kSliceSmall).total;
+    need = larger < need ? larger : need;
+  }
   if (need && (!workspace || workspace_bytes < need))
     return fail(BPC_EWORKSPACE, "workspace of %zu bytes given, %zu needed", workspace ? workspace_bytes : 0, need);
   const int G = Hq / Hkv;

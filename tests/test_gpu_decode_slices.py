@@ -63,3 +63,23 @@ def test_workspace_of_larger_slices():
     assert torch.equal(a[1], b[1]) and float((a[0] - b[0]).abs().max()) < 1e-4
     with pytest.raises(bpc.BPCError):
         step(B, G, H, N, L, k, ws_bytes=small // 2)
+
+
+def test_per_head_workspace_of_larger_slices():
+    B, G, H, N, L, k = 1, 4, 8, 16384, 64, 328
+    g = torch.Generator(device=DEV).manual_seed(5)
+    q = torch.randn(B, G * H, 128, generator=g, device=DEV).to(torch.bfloat16)
+    K = torch.randn(B, H, N, 128, generator=g, device=DEV).to(torch.bfloat16)
+    P = torch.randn(B, H, L, 128, generator=g, device=DEV)
+    codes = torch.randint(-2 ** 31, 2 ** 31, (B, H, N, L // 32), generator=g, device=DEV).int()
+    full = bpc.decode_per_head_workspace_bytes(B, G * H, H, N, L, k)
+    # 256 slices of 2048 keys; of 4096, half the records and partials
+    small = full - 128 * (4 * (68 + 4 + 132 + 128) + 4 * 130)
+    got = []
+    for size in (full, small + 512):
+        idx = torch.empty(B, G * H, k, dtype=torch.int32, device=DEV)
+        ws = torch.zeros(size, dtype=torch.uint8, device=DEV)
+        got.append((bpc.decode_attention_per_head(q, K, K, codes, P, k, idx_out=idx, workspace=ws), idx))
+    assert torch.equal(got[0][1], got[1][1]) and float((got[0][0] - got[1][0]).abs().max()) < 1e-4
+    with pytest.raises(bpc.BPCError):
+        bpc.decode_attention_per_head(q, K, K, codes, P, k, workspace=ws[: small // 2])
