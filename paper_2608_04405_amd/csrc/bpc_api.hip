@@ -119,15 +119,17 @@ BuildLayout build_layout(int B, int Hkv, int N, int L) {
     return at;
   };
   b.off_p64 = take(BH * (size_t)L * kHeadDim * sizeof(double));  // P widened to fp64
-  const size_t shared = o;
   b.nchunks = (N + kBuildChunk - 1) / kBuildChunk;
   b.off_part = take(BH * b.nchunks * (size_t)kHeadDim * sizeof(double));  // one fp64 tree sum per chunk and coordinate
   b.nfold = b.nchunks > 8 * kBuildFold ? (b.nchunks + kBuildFold - 1) / kBuildFold : 0;
+  const size_t shared = o;
   b.off_fold = take(BH * b.nfold * (size_t)kHeadDim * sizeof(double));  // and per block of chunks
   b.off_g64 = take((size_t)L * kHeadDim * sizeof(double));              // G widened to fp64
   b.total_min = o;
 
   o = shared;
+  b.off_sfold = take(BH * ((b.nchunks + kDenseFold - 1) / kDenseFold) * (size_t)kHeadDim * sizeof(double));
+  b.off_mode = take(BH * 4 * sizeof(int));
   const size_t nblk = ((size_t)N + 63) / 64;
   // two workgroups per compute unit, all resident at once, while that leaves
   // each wavefront a block

@@ -78,6 +78,7 @@ constexpr int kBuildChunk = 64 * kBuildGroups;     // keys per workgroup (one ch
 // chunk sums folded per workgroup before the per-(b, h) reduction, when a
 // (b, h) has more than 8 such blocks of chunks
 constexpr int kBuildFold = 32;
+constexpr int kDenseFold = 16;  // and per round in a (b, h) that has left the scan
 // fp64 values per (b, h) and coordinate that the scanning build carries from bit to bit
 constexpr int kScanStats = 7;
 constexpr int kScanMinKeys = 40960;  // keys of the whole call up to which the rebuilding passes are faster
@@ -113,10 +114,11 @@ struct BuildLayout {
   int nfold;  // aligned blocks of kBuildFold chunks folded first, or 0
   // the recomputing build: needs the least memory
   size_t off_part, off_fold, off_p64, off_g64, total_min;
-  // the scanning build (P64 shared with the above): workgroups per (b, h) and
-  // 64-key blocks per workgroup of its passes
+  // the scanning build (P64 and the chunk sums shared with the above):
+  // workgroups per (b, h) and 64-key blocks per workgroup of its passes
   int scan_wgs, scan_blocks;
-  size_t off_psum, off_pcnt, off_node, off_planes, off_knorm, off_stat, off_cmat, off_corr, off_tab, off_bound, total;
+  size_t off_psum, off_pcnt, off_node, off_planes, off_knorm, off_stat, off_cmat, off_corr, off_tab, off_bound,
+      off_sfold, off_mode, total;
   size_t total_ck;  // with the room of an fp64 residual per key, which no build needs any more
 };
 

@@ -11,6 +11,7 @@
 #include <type_traits>
 
 #include "bpc_internal.h"
+#include "build_tree.h"
 #include "mfma_split.h"
 
 namespace bpc {
@@ -49,45 +50,6 @@ namespace bpc {
 // whole build) for memory traffic.
 // ============================================================================
 
-// the partner lane's value at lane ^ M (quad permutes for 1 and 2)
-template <int M>
-__device__ __forceinline__ double xor_lane(double x) {
-  if constexpr (M == 1 || M == 2) {
-    constexpr int ctrl = (M == 1) ? 0xB1 : 0x4E;  // quad_perm [1,0,3,2] / [2,3,0,1]
-    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(x), ctrl, 0xF, 0xF, false);
-    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(x), ctrl, 0xF, 0xF, false);
-    return __hiloint2double(hi, lo);
-  } else {
-    return __shfl_xor(x, M, 64);
-  }
-}
-
-// A wavefront-uniform address of data that no kernel writes while this one
-// runs, in the constant address space so that loads through it are scalar.
-template <typename T>
-using const_ptr = const __attribute__((address_space(4))) T*;
-
-template <typename T>
-__device__ __forceinline__ const_ptr<T> uniform_ptr(const T* p) {
-  const uint64_t a = reinterpret_cast<uint64_t>(p);
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a);
-  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
-  return (const_ptr<T>)(((uint64_t)hi << 32) | lo);
-}
-
-// one reduce-scatter level: lanes l and l ^ (1 << K) add their halves of the
-// 2 * HALF coordinates they carry; the lane with bit K clear keeps the lower half
-template <int K, int HALF>
-__device__ __forceinline__ void rs_level(double (&v)[32], int lane) {
-  const bool upper = (lane >> K) & 1;
-#pragma unroll
-  for (int e = 0; e < HALF; ++e) {
-    const double send = upper ? v[e] : v[HALF + e];
-    const double keep = upper ? v[HALF + e] : v[e];
-    v[e] = dadd(keep, xor_lane<1 << K>(send));
-  }
-}
-
 __global__ void build_prep_kernel(const float* __restrict__ G, double* __restrict__ G64, int n) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) G64[i] = (double)G[i];
@@ -116,15 +78,7 @@ __global__ __launch_bounds__(kBuildThreads) void build_bit_kernel(
   for (int w = 0; w < W; ++w) cw[w] = 0u;
   uint32_t* crow = codes + b * sC_b + h * sC_h + (int64_t)(valid ? key : 0) * W;
   if (valid) {
-    const uint16_t* krow = K + b * sK_b + h * sK_h + (int64_t)key * sK_n + 32 * c;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const uint4 v = *reinterpret_cast<const uint4*>(krow + 8 * q);
-      const uint32_t wd[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-      for (int e = 0; e < 8; ++e)
-        r[8 * q + e] = bf16_to_f64((uint16_t)((e & 1) ? (wd[e >> 1] >> 16) : (wd[e >> 1] & 0xFFFFu)));
-    }
+    load_block(K + b * sK_b + h * sK_h + (int64_t)key * sK_n + 32 * c, r);
 #pragma unroll
     for (int w = 0; w < W; ++w)
       if (32 * w < bit) cw[w] = crow[w];
@@ -133,18 +87,7 @@ __global__ __launch_bounds__(kBuildThreads) void build_bit_kernel(
     for (int e = 0; e < 32; ++e) r[e] = 0.0;  // never contributes: padded below
   }
   // the residual after bits 0 .. bit - 1
-  const_ptr<double> prow = uniform_ptr(P64 + (size_t)bh * L * kHeadDim + 32 * c);
-#pragma unroll
-  for (int w = 0; w < W; ++w) {
-    const int nb = min(32, bit - 32 * w);
-    const uint32_t word = cw[w];
-    for (int ib = 0; ib < nb; ++ib) {
-      const double sg = ((word >> ib) & 1u) ? -1.0 : 1.0;
-      const_ptr<double> p = prow + (size_t)(32 * w + ib) * kHeadDim;
-#pragma unroll
-      for (int e = 0; e < 32; ++e) r[e] = __builtin_fma(sg, p[e], r[e]);
-    }
-  }
+  remove_bits<W>(r, cw, bit, uniform_ptr(P64 + (size_t)bh * L * kHeadDim + 32 * c));
   // a_j = R_j . g (four blocks of 32, ascending, combined ((b0 + b1) + (b2 + b3)))
   const_ptr<double> g = uniform_ptr(G64 + (size_t)bit * kHeadDim + 32 * c);
   double acc = 0.0;
@@ -162,22 +105,9 @@ __global__ __launch_bounds__(kBuildThreads) void build_bit_kernel(
       if (lane == 0 && m) atomicAdd(&frag, __popcll(m));
     }
   }
-  // u_j R_j (exact), keys past N padded with +0, and the tree over the
-  // group's 64 keys: after the five reduce-scatter levels lane l carries the
-  // coordinate whose index is l's low five bits reversed, summed over its
-  // half of the group; the xor-32 step adds the two halves
-  double v[32];
-#pragma unroll
-  for (int e = 0; e < 32; ++e) v[e] = valid ? (u ? r[e] : -r[e]) : 0.0;
-  rs_level<0, 16>(v, lane);
-  rs_level<1, 8>(v, lane);
-  rs_level<2, 4>(v, lane);
-  rs_level<3, 2>(v, lane);
-  rs_level<4, 1>(v, lane);
-  const double s = dadd(v[0], xor_lane<32>(v[0]));
+  const double s = group_tree(r, valid, u, lane);
   if (lane < 32) {
-    const int e = (int)(__brev((uint32_t)lane) >> 27);
-    groot[grp][32 * c + e] = s;
+    groot[grp][32 * c + group_tree_index(lane)] = s;
   }
   __syncthreads();
   static_assert(kBuildGroups == 2, "one tree level across the key groups");
@@ -195,18 +125,8 @@ __global__ __launch_bounds__(kHeadDim) void build_fold_kernel(const double* __re
                                                               double* __restrict__ fold, int nfold) {
   const int bh = blockIdx.y, x = blockIdx.x, d = threadIdx.x;
   const int begin = x * kBuildFold;
-  int c = min(kBuildFold, nchunks - begin);
-  const double* src = part + ((size_t)bh * nchunks + begin) * kHeadDim + d;
-  double v[kBuildFold];
-#pragma unroll
-  for (int e = 0; e < kBuildFold; ++e) v[e] = (e < c) ? src[(size_t)e * kHeadDim] : 0.0;
-#pragma unroll
-  for (int w = kBuildFold / 2; w >= 1; w >>= 1) {
-#pragma unroll
-    for (int i = 0; i < w; ++i) v[i] = (2 * i + 1 < c) ? dadd(v[2 * i], v[2 * i + 1]) : v[2 * i];
-    c = (c + 1) >> 1;
-  }
-  fold[((size_t)bh * nfold + x) * kHeadDim + d] = v[0];
+  fold[((size_t)bh * nfold + x) * kHeadDim + d] =
+      fold_sums<kBuildFold>(part + ((size_t)bh * nchunks + begin) * kHeadDim + d, min(kBuildFold, nchunks - begin));
 }
 
 // One workgroup per (b, h): thread (blk, d) folds an aligned block of S

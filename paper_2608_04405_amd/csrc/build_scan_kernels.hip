@@ -30,10 +30,22 @@
 // column's tree is summed in the reference order.  Columns whose sums are exact
 // certify with B = 0.  Columns with a non-finite key, zero columns with a -0 in
 // them and vanished columns whose sum may be -0 always take the exact route.
+//
+// A (b, h) in which that happens often (non-finite keys, few different keys,
+// sums that fit the signs exactly) would have one workgroup sum column after
+// column, or decide every sign three times, on every bit: at 8 x 16384 keys and
+// L = 64 a NaN in one head made a build of 1.2 ms one of 767.  It leaves the
+// scan for good: from the bit in question on its workgroups rebuild the
+// residuals and form the tree of every column (dense_pass), as the rebuilding
+// passes do and at 0.7 to 1.1 times their speed (those 767 ms become 2.8; 16
+// different keys, repeated, 52 -> 3.6; 3.2 by the rebuilding passes).  That bit is repeated in the next launch, so such
+// a (b, h) runs one bit behind the others and the build ends with one more pair
+// of launches, in which they do nothing.
 
 #pragma clang fp contract(off)
 
 #include "bpc_internal.h"
+#include "build_tree.h"
 #include "mfma_split.h"
 
 namespace bpc {
@@ -260,10 +272,152 @@ __device__ __forceinline__ double lane_reference_decision(const uint16_t* row, c
 constexpr int kScanMany = 16;
 
 // ---------------------------------------------------------------------------
+// What a (b, h) does (x of `mode`), the columns redone so far (y) and the tiles
+// of 64 keys whose signs went to the reference arithmetic (z).  The sign pass
+// reads the state from its bounds, which it needs anyway: alpha1 = -state.
+// ---------------------------------------------------------------------------
+constexpr int kScanning = 0, kDenseFirst = 1, kDense = 2;  // kDenseFirst: the bit's fragile decisions are counted already
+// Columns over the whole build beyond which the scan is left.  Of random keys a
+// (b, h) redoes less than one in a build; each holds up the pass by up to 7 ms (a
+// million keys).
+constexpr int kDenseColumns = 8;
+__device__ __forceinline__ bool leave_scan(int columns, int tiles, int nblk) {
+  return columns > kDenseColumns || tiles > 2 * nblk;  // two whole bits of uncertain signs
+}
+
+__device__ __forceinline__ void load_row(double (&p)[16], const_ptr<double> src) {
+#pragma unroll
+  for (int e = 0; e < 16; ++e) p[e] = src[e];
+}
+// Uses the values, so that scalar loads issued after this point are not waited
+// for with them (these return in no order and are waited for all together).
+__device__ __forceinline__ void wait_row(double (&p)[16]) {
+#pragma unroll
+  for (int e = 0; e < 16; e += 8)
+    asm volatile("" ::"s"(p[e]), "s"(p[e + 1]), "s"(p[e + 2]), "s"(p[e + 3]), "s"(p[e + 4]), "s"(p[e + 5]),
+                 "s"(p[e + 6]), "s"(p[e + 7]));
+}
+
+// One bit of a (b, h) that has left the scan, for chunks [begin, end): signs,
+// bit planes and the tree sum of every column over each chunk, all in the
+// reference arithmetic.  Wavefront c owns coordinates [32 c, 32 c + 32); a lane
+// takes two keys at a time, one of each half of the chunk, so that every scalar
+// load of P serves both, and half a row of P is loaded ahead.  Bound by the fp64
+// subtractions and the tree; 8 x 131072 keys, L = 64, all heads: 20 ms a build
+// (25 with one key per lane, 27 with two and no load ahead; the rebuilding passes,
+// which keep more wavefronts in flight, 15).
+template <int W>
+__device__ __forceinline__ void dense_pass(const uint16_t* Kb, int64_t sK_n, int N, int bit, int begin, int end,
+                                           const float* g, const double* P64b, uint64_t* planes, double* part,
+                                           double (*xch)[4][64], double (*groot)[kHeadDim],
+                                           unsigned long long* fragile) {
+  constexpr int NP = W == 4 ? 2 : 1;
+  static_assert(kBuildGroups == 2, "two keys per lane, one tree level across them");
+  const int lane = threadIdx.x & 63;
+  const int c = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const const_ptr<double> prow = uniform_ptr(P64b + 32 * c);
+  const const_ptr<float> gp = uniform_ptr(g + 32 * c);
+  int nfrag = 0;
+  for (int chunk = begin; chunk < end; ++chunk) {
+    double r[2][32];
+    uint32_t cw[2][2 * NP];
+    uint64_t* pl = planes + (size_t)chunk * 2 * (32 * W);
+    const int key0 = chunk * kBuildChunk + lane;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const bool live = chunk * kBuildChunk + 64 * q < N;
+#pragma unroll
+      for (int x = 0; x < NP; ++x) {
+        const uint64_t col = live && lane + 64 * x < bit ? pl[32 * W * q + lane + 64 * x] : 0ull;
+        cw[q][2 * x] = (uint32_t)col, cw[q][2 * x + 1] = (uint32_t)(col >> 32);
+        if (bit > 64 * x) transpose64(cw[q][2 * x], cw[q][2 * x + 1]);
+      }
+      if (key0 + 64 * q < N) {
+        load_block(Kb + (int64_t)(key0 + 64 * q) * sK_n + 32 * c, r[q]);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 32; ++e) r[q][e] = 0.0;
+      }
+    }
+    // half a row of P in use, the other half on its way
+    double pa[16], pb[16];
+    const_ptr<double> next = prow;
+    load_row(pa, next);
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+      const int nb = min(32, bit - 32 * w);
+      for (int ib = 0; ib < nb; ++ib) {
+        const double s0 = ((cw[0][w] >> ib) & 1u) ? -1.0 : 1.0, s1 = ((cw[1][w] >> ib) & 1u) ? -1.0 : 1.0;
+        wait_row(pa);
+        load_row(pb, next + 16);
+        if (32 * w + ib + 1 < bit) next += kHeadDim;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          r[0][e] = __builtin_fma(s0, pa[e], r[0][e]);
+          r[1][e] = __builtin_fma(s1, pa[e], r[1][e]);
+        }
+        wait_row(pb);
+        load_row(pa, next);
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          r[0][16 + e] = __builtin_fma(s0, pb[e], r[0][16 + e]);
+          r[1][16 + e] = __builtin_fma(s1, pb[e], r[1][16 + e]);
+        }
+      }
+    }
+    double acc0 = 0.0, acc1 = 0.0;
+#pragma unroll
+    for (int e = 0; e < 32; ++e) {
+      acc0 = dadd(acc0, dmul(r[0][e], (double)gp[e]));
+      acc1 = dadd(acc1, dmul(r[1][e], (double)gp[e]));
+    }
+    xch[0][c][lane] = acc0, xch[1][c][lane] = acc1;
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const double a = dadd(dadd(xch[q][0][lane], xch[q][1][lane]), dadd(xch[q][2][lane], xch[q][3][lane]));
+      const bool u = a >= 0.0, valid = key0 + 64 * q < N;
+      if (c == 0) {
+        const unsigned long long M = __ballot(valid && u);
+        nfrag += __popcll(__ballot(valid && fragile_decision(a)));
+        if (lane == 0 && chunk * kBuildChunk + 64 * q < N) pl[32 * W * q + bit] = M;
+      }
+      const double s = group_tree(r[q], valid, u, lane);
+      if (lane < 32) groot[q][32 * c + group_tree_index(lane)] = s;
+    }
+    __syncthreads();
+    if (threadIdx.x < kHeadDim)
+      part[(size_t)chunk * kHeadDim + threadIdx.x] = dadd(groot[0][threadIdx.x], groot[1][threadIdx.x]);
+  }
+  if (fragile && threadIdx.x == 0 && nfrag) atomicAdd(fragile, (unsigned long long)nfrag);
+}
+
+// The sum of every column from its chunks' tree sums, by the whole workgroup:
+// blocks of kDenseFold folded from one array into the other.  Thread d < 128 returns
+// column d's.
+template <int NTH>
+__device__ __forceinline__ double dense_sum(double* part, double* fold, int nchunks) {
+  const int d = threadIdx.x & (kHeadDim - 1);
+  double* src = part;
+  double* dst = fold;
+  for (int cnt = nchunks; cnt > 1;) {
+    const int nb = (cnt + kDenseFold - 1) / kDenseFold;
+    for (int x = threadIdx.x / kHeadDim; x < nb; x += NTH / kHeadDim)
+      dst[(size_t)x * kHeadDim + d] =
+          fold_sums<kDenseFold>(src + (size_t)x * kDenseFold * kHeadDim + d, min(kDenseFold, cnt - x * kDenseFold));
+    __syncthreads();
+    double* t = src;
+    src = dst, dst = t, cnt = nb;
+  }
+  return src[d];
+}
+
+// ---------------------------------------------------------------------------
 // One bit: sign and bit plane of every key, and per workgroup
 // sum_j u_j k_j (fp64) and the popcounts against the earlier bit planes.
 // Bound by the read of the keys; per 64 keys a wavefront issues about 460
 // vector instructions, 384 of them the fp64 sum (widen, convert, fused add).
+// (The launch after the last bit is for the (b, h) that have left the scan.)
 // ---------------------------------------------------------------------------
 template <int W>
 __global__ __launch_bounds__(kScanThreads, 2) void build_sign_kernel(
@@ -271,6 +425,7 @@ __global__ __launch_bounds__(kScanThreads, 2) void build_sign_kernel(
     int blocks_per_wg, int nblk, const float* __restrict__ G, const float* __restrict__ P,
     const uint16_t* __restrict__ knorm, const float* __restrict__ tab, const double* __restrict__ corr, const float4* __restrict__ bound,
     uint64_t* __restrict__ planes, double* __restrict__ psum, uint32_t* __restrict__ pcnt,
+    const double* __restrict__ P64, double* __restrict__ part, int4* __restrict__ mode,
     unsigned long long* __restrict__ fragile) {
   constexpr int L = 32 * W;
   constexpr int NP = W == 4 ? 2 : 1;  // bit planes per lane
@@ -286,7 +441,7 @@ __global__ __launch_bounds__(kScanThreads, 2) void build_sign_kernel(
   const uint16_t* Kb = K + b * sK_b + h * sK_h;
   const uint32_t row_bytes = (uint32_t)sK_n * 2u;
   const float* Pb = P + (size_t)bh * L * kHeadDim;
-  const float* g = G + (size_t)bit * kHeadDim;
+  const float* g = G + (size_t)min(bit, L - 1) * kHeadDim;
   const double* cb = corr + (size_t)bh * L;
   const int nbytes = (bit + 7) >> 3;  // code bytes that hold earlier bits
   const int blk_begin = blockIdx.x * blocks_per_wg + wave;
@@ -308,6 +463,17 @@ __global__ __launch_bounds__(kScanThreads, 2) void build_sign_kernel(
   }
   const float4 bd = bound[bh];  // alpha1, beta1, alpha2, beta2
   __syncthreads();
+  if (bd.x < 0.f) {
+    const int chunk0 = (int)blockIdx.x * blocks_per_wg / kBuildGroups;
+    dense_pass<W>(Kb, sK_n, N, bit - 1, chunk0,
+                  min(chunk0 + blocks_per_wg / kBuildGroups, (nblk + kBuildGroups - 1) / kBuildGroups),
+                  G + (size_t)(bit - 1) * kHeadDim, P64 + (size_t)bh * L * kHeadDim, planes + (size_t)bh * nblk * L,
+                  part + (size_t)bh * ((nblk + kBuildGroups - 1) / kBuildGroups) * kHeadDim,
+                  reinterpret_cast<double(*)[4][64]>(&tab_s[0][0]), red,
+                  bd.x == -(float)kDense ? fragile : nullptr);
+    return;
+  }
+  if (bit >= L) return;
 
   double acc[32];
 #pragma unroll
@@ -374,6 +540,7 @@ __global__ __launch_bounds__(kScanThreads, 2) void build_sign_kernel(
       todo = __ballot(!sure2);
       if (__popcll(todo) > kScanMany) {
         const double ar = lane_reference_decision<W>(row, Pb, g, bit, cw);
+        if (lane == 0) atomicAdd(&mode[bh].z, 1);
         if (!sure2) {
           u = ar >= 0.0;
           nfrag += fragile_decision(ar) ? 1 : 0;
@@ -459,44 +626,62 @@ __device__ __forceinline__ void two_sum(double a, double b, double& s, double& e
 // arithmetic, by the whole workgroup.  planes: the (b, h)'s bit planes, bits
 // 0 .. bit of 64 keys at a stride of L words; pcol: P[t][d] for t < bit; node: global
 // scratch of two doubles per chunk.
+//
+// A wavefront takes eight blocks of 64 keys at a time, one key of each per lane
+// (eight independent chains), whose signs it gets by transposing the bit planes
+// as the sign pass does.  Bound by vector issue (four instructions per key and
+// bit) on one compute unit.  A column of a million keys at L = 128: 4 to 7 ms (8
+// to 15 with a chunk per lane, each reading its bytes of every plane); the whole
+// build of 8 x 1048576 keys 105 -> 82 ms.
 template <int W, int NTH>
 __device__ double reference_column(const uint16_t* Kd, int64_t sK_n, const uint64_t* planes, int N, int bit,
                                    const double* pcol, double* node) {
-  const int nch = (N + kBuildChunk - 1) / kBuildChunk;
-  for (int c = threadIdx.x; c < nch; c += NTH) {
-    double s0 = 0.0, s1 = 0.0, s2 = 0.0, root = 0.0;
-    for (int q = 0; q < kBuildChunk / 8; ++q) {
-      // eight rows at a time (one byte of each bit plane), eight independent chains
-      const int j0 = c * kBuildChunk + 8 * q;
-      double v[8];
+  constexpr int NP = W == 4 ? 2 : 1;
+  constexpr int Q = 8;  // blocks per turn
+  const int lane = threadIdx.x & 63;
+  const int nblk = (N + 63) / 64, nch = (N + kBuildChunk - 1) / kBuildChunk;
+  for (int b0 = Q * (threadIdx.x >> 6); b0 < nblk; b0 += Q * (NTH / 64)) {
+    double v[Q];
+    uint32_t cw[Q][2 * NP];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) v[e] = bf16_to_f64(Kd[(int64_t)min(j0 + e, N - 1) * sK_n]);
-      const uint8_t* pb = reinterpret_cast<const uint8_t*>(planes + (size_t)(min(j0, N - 1) >> 6) * (32 * W)) + (q & 7);
-#pragma unroll 8
-      for (int t = 0; t < bit; ++t) {
-        const uint32_t s = pb[8 * t];
-        const double p = pcol[t];
+    for (int q = 0; q < Q; ++q) {
+      const int blk = min(b0 + q, nblk - 1);
+      v[q] = bf16_to_f64(Kd[(int64_t)min(blk * 64 + lane, N - 1) * sK_n]);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = __builtin_fma(((s >> e) & 1u) ? -1.0 : 1.0, p, v[e]);
+      for (int x = 0; x < NP; ++x) {
+        const uint64_t col = lane + 64 * x <= bit ? planes[(size_t)blk * (32 * W) + lane + 64 * x] : 0ull;
+        cw[q][2 * x] = (uint32_t)col, cw[q][2 * x + 1] = (uint32_t)(col >> 32);
       }
-      const uint32_t su = pb[8 * bit];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) v[e] = j0 + e >= N ? 0.0 : ((su >> e) & 1u) ? v[e] : -v[e];
-      double y = ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
-      // the 16 groups of eight of a chunk as a binary counter
-      if (q & 1) {
-        y = s0 + y;
-        if (q & 2) {
-          y = s1 + y;
-          if (q & 4) {
-            y = s2 + y;
-            if (q & 8) root = root + y;
-            else root = y;
-          } else s2 = y;
-        } else s1 = y;
-      } else s0 = y;
     }
-    node[c] = root;
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+#pragma unroll
+      for (int x = 0; x < NP; ++x) transpose64(cw[q][2 * x], cw[q][2 * x + 1]);
+    bool u[Q];
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+      const int nb = min(32, bit - 32 * w);
+#pragma unroll 2
+      for (int t = 0; t < nb; ++t) {
+        const double p = pcol[32 * w + t];
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+          v[q] = __builtin_fma(__hiloint2double((int)(0x3FF00000u | ((cw[q][w] >> t) << 31)), 0), p, v[q]);
+      }
+      if (w == bit >> 5) {
+#pragma unroll
+        for (int q = 0; q < Q; ++q) u[q] = (cw[q][w] >> (bit & 31)) & 1u;
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      v[q] = (b0 + q) * 64 + lane >= N ? 0.0 : u[q] ? v[q] : -v[q];
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) v[q] = v[q] + __shfl_xor(v[q], o, 64);
+    }
+#pragma unroll
+    for (int q = 0; q < Q; q += 2)
+      if (lane == 0 && (b0 + q) / 2 < nch) node[(b0 + q) / 2] = v[q] + v[q + 1];
   }
   double* src = node;
   double* dst = node + nch;
@@ -537,8 +722,9 @@ __global__ __launch_bounds__(kSolveThreads) void build_solve_kernel(
     const uint16_t* __restrict__ K, int64_t sK_b, int64_t sK_h, int64_t sK_n, int Hkv, int N, int bit, int nwg,
     int chain, const float* __restrict__ G, const uint64_t* __restrict__ planes,
     const double* __restrict__ psum, const uint32_t* __restrict__ pcnt, const uint32_t* __restrict__ pext,
-    double* __restrict__ node, float* __restrict__ P, double* __restrict__ P64, double* __restrict__ stat, double* __restrict__ cmat,
-    double* __restrict__ corr, float* __restrict__ tab, float4* __restrict__ bound) {
+    double* __restrict__ node, float* __restrict__ P, double* __restrict__ P64, double* __restrict__ stat,
+    double* __restrict__ cmat, double* __restrict__ corr, float* __restrict__ tab, float4* __restrict__ bound,
+    double* __restrict__ part, double* __restrict__ fold, int4* __restrict__ mode) {
   constexpr int L = 32 * W;
   constexpr int NS = kSolveSlices;
   constexpr int NX = (8 * L + kSolveThreads - 1) / kSolveThreads;  // rounds of eight lanes per later bit
@@ -561,7 +747,8 @@ __global__ __launch_bounds__(kSolveThreads) void build_solve_kernel(
   // Every load this call will need is issued here: what follows is a chain of
   // short steps between barriers, bound by their latency.
   const int next = bit + 1;
-  const int part = tid & 7;
+  const int eighth = tid & 7;
+  const int4 md = mode[bh];
   double pv[L / NS];
 #pragma unroll
   for (int x = 0; x < L / NS; ++x)
@@ -574,7 +761,7 @@ __global__ __launch_bounds__(kSolveThreads) void build_solve_kernel(
   for (int r = 0; r < NX; ++r) {
     const int sx = min((tid >> 3) + r * (kSolveThreads / 8), L - 1);
 #pragma unroll
-    for (int x = 0; x < 4; ++x) gs[r][x] = reinterpret_cast<const float4*>(G + (size_t)sx * kHeadDim + 16 * part)[x];
+    for (int x = 0; x < 4; ++x) gs[r][x] = reinterpret_cast<const float4*>(G + (size_t)sx * kHeadDim + 16 * eighth)[x];
   }
   const double c_old = tid < bit && next < L ? cmat[((size_t)bh * L + next) * L + tid] : 0.0;
   float g0 = 0.f, g1 = 0.f;
@@ -598,12 +785,27 @@ __global__ __launch_bounds__(kSolveThreads) void build_solve_kernel(
     s += ((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + (x[6] + x[7]));
     cn += ((c[0] + c[1]) + (c[2] + c[3])) + ((c[4] + c[5]) + (c[6] + c[7]));
   }
+  const int nch = (N + kBuildChunk - 1) / kBuildChunk;
+  if (bit >= 0 && md.x != kScanning) {
+    const double T = dense_sum<kSolveThreads>(part + (size_t)bh * nch * kHeadDim,
+                                              fold + (size_t)bh * ((nch + kDenseFold - 1) / kDenseFold) * kHeadDim, nch);
+    if (tid < kHeadDim) {
+      const size_t at = ((size_t)bh * L + bit - 1) * kHeadDim + d;
+      const float p = (float)(T / dN);
+      P[at] = p;
+      P64[at] = (double)p;
+    }
+    if (tid == 0) bound[bh].x = -(float)kDense;
+    return;
+  }
+  if (bit >= L) return;
   if (tid < L) n_s[tid] = 0;
   if (tid == 0) nredo = 0;
   __syncthreads();
   if (d <= bit) atomicAdd(&n_s[d], cn);
 
   if (bit < 0) {
+    if (tid == 0) mode[bh] = make_int4(kScanning, 0, 0, 0);
     uint32_t mx = 0u, mn = 0x7FFFu, nz = 0u;
     for (int w = sl8; w < nwg; w += NS) {
       const uint32_t x = pext[((size_t)bh * nwg + w) * kHeadDim + d];
@@ -688,13 +890,18 @@ __global__ __launch_bounds__(kSolveThreads) void build_solve_kernel(
     __syncthreads();
     const int nr = nredo;
     const int nblk = (N + 63) / 64;
+    if (leave_scan(md.y + nr, md.z, nblk)) {  // this bit again, by dense_pass
+      if (tid == 0) mode[bh].x = kDense, bound[bh].x = -(float)kDenseFirst;
+      return;
+    }
+    if (nr && tid == 0) mode[bh].y = md.y + nr;
     for (int r = 0; r < nr; ++r) {
       const int dd = redo[r];
       if (tid < bit) col_s[tid] = P64[((size_t)bh * L + tid) * kHeadDim + dd];
       __syncthreads();
       const double T = reference_column<W, kSolveThreads>(K + b * sK_b + h * sK_h + dd, sK_n,
                                                          planes + (size_t)bh * nblk * L, N, bit, col_s,
-                                                         node + (size_t)bh * 2 * ((N + kBuildChunk - 1) / kBuildChunk));
+                                                         node + (size_t)bh * 2 * nch);
       if (tid == 0) p_s[dd] = (double)(float)(T / dN);
     }
     __syncthreads();
@@ -723,7 +930,7 @@ __global__ __launch_bounds__(kSolveThreads) void build_solve_kernel(
       double c = 0.0;
 #pragma unroll
       for (int x = 0; x < 4; ++x) {
-        const double* pp = p_s + 16 * part + 4 * x;
+        const double* pp = p_s + 16 * eighth + 4 * x;
         c = __builtin_fma(pp[0], (double)gs[r][x].x, c);
         c = __builtin_fma(pp[1], (double)gs[r][x].y, c);
         c = __builtin_fma(pp[2], (double)gs[r][x].z, c);
@@ -732,7 +939,7 @@ __global__ __launch_bounds__(kSolveThreads) void build_solve_kernel(
       c += __shfl_xor(c, 1, 64);
       c += __shfl_xor(c, 2, 64);
       c += __shfl_xor(c, 4, 64);
-      if (part == 0) {
+      if (eighth == 0) {
         cmat[((size_t)bh * L + sx) * L + bit] = c;
         if (sx == next) c_s[bit] = c;
       }
@@ -815,6 +1022,9 @@ static void launch_build_scan_W(const BuildArgs& a, const BuildLayout& lay) {
   double* corr = reinterpret_cast<double*>(ws + lay.off_corr);
   float* tab = reinterpret_cast<float*>(ws + lay.off_tab);
   float4* bound = reinterpret_cast<float4*>(ws + lay.off_bound);
+  double* part = reinterpret_cast<double*>(ws + lay.off_part);
+  double* fold = reinterpret_cast<double*>(ws + lay.off_sfold);
+  int4* mode = reinterpret_cast<int4*>(ws + lay.off_mode);
   const dim3 grid(lay.scan_wgs, BH);
   const int bpw = lay.scan_blocks, nblk = (a.N + 63) / 64;
   // additions one key passes through on this side: a lane's own chain, the
@@ -822,13 +1032,14 @@ static void launch_build_scan_W(const BuildArgs& a, const BuildLayout& lay) {
   const int chain = bpw + lay.scan_wgs / 4 + 32;
   build_stat_kernel<<<grid, kScanThreads, 0, a.stream>>>(a.K, a.sK_b, a.sK_h, a.sK_n, a.Hkv, a.N, bpw, psum, pcnt,
                                                          knorm, nblk);
-  for (int bit = -1; bit < L; ++bit) {
+  for (int bit = -1; bit <= L; ++bit) {
     if (bit >= 0)
-      build_sign_kernel<W><<<grid, kScanThreads, 0, a.stream>>>(a.K, a.sK_b, a.sK_h, a.sK_n, a.Hkv, a.N, bit, bpw,
-                                                                nblk, a.G, a.P, knorm, tab, corr, bound, planes, psum, pcnt, a.fragile);
+      build_sign_kernel<W><<<grid, kScanThreads, 0, a.stream>>>(a.K, a.sK_b, a.sK_h, a.sK_n, a.Hkv, a.N, bit, bpw, nblk,
+                                                                a.G, a.P, knorm, tab, corr, bound, planes, psum, pcnt,
+                                                                P64, part, mode, a.fragile);
     build_solve_kernel<W><<<BH, kSolveThreads, 0, a.stream>>>(a.K, a.sK_b, a.sK_h, a.sK_n, a.Hkv, a.N, bit,
-                                                              lay.scan_wgs, chain, a.G, planes, psum, pcnt, pcnt, node, a.P, P64, stat, cmat, corr, tab,
-                                                              bound);
+                                                              lay.scan_wgs, chain, a.G, planes, psum, pcnt, pcnt, node,
+                                                              a.P, P64, stat, cmat, corr, tab, bound, part, fold, mode);
   }
   build_codes_kernel<W><<<dim3((nblk + 3) / 4, BH), kScanThreads, 0, a.stream>>>(planes, a.Hkv, a.N, nblk, a.codes,
                                                                                  a.sC_b, a.sC_h);

@@ -154,3 +154,29 @@ def test_sign_of_a_vanished_column(L):
     assert bool((res[1][0][:, :36, 1, 0].view(torch.int32) == -2 ** 31).all())  # the case arises
     assert_same(res)
     assert_same(both(K, G, N - 1))
+
+
+# A (b, h) whose columns or signs certify too rarely leaves the scan for the
+# residuals, one bit behind the others: few different keys, a NaN, every sign
+# uncertain, beside heads that go on scanning; one chunk, one fold of chunks and
+# several, whole and ragged.
+@pytest.mark.parametrize("L,N,H", [(32, 100, 420), (64, 643, 72), (128, 640, 72), (64, 2049, 24), (32, 5000, 12),
+                                   (64, 70001, 3)])
+@pytest.mark.parametrize("form", ["two_keys", "few_keys", "nan", "negative_zeros", "rank_one"])
+def test_leaving_the_scan(form, L, N, H):
+    print(f"[build scan] leaving: {form} L={L} N={N} H={H}", flush=True)
+    K = keys(N, H=H, seed=L + N)
+    part = K[:, ::3]
+    if form == "two_keys":
+        part[:] = part[:, :, :1].clone()
+        part[:, :, ::3] = -0.5 * part[:, :, :1].clone() + 1
+    elif form == "few_keys":
+        part[:] = part[:, :, :16].repeat(1, 1, -(-N // 16), 1)[:, :, :N].clone()
+    elif form == "nan":
+        part[:, :, N // 3, 5] = float("nan")
+    elif form == "negative_zeros":
+        part[..., 64:] = 0
+        part[:, :, ::2, 64:] = -part[:, :, ::2, 64:]
+    elif form == "rank_one":
+        part[:] = (part[:, :, :1].float() * torch.randint(-3, 4, (1, 1, N, 1), device=DEV)).to(torch.bfloat16)
+    assert_same(both(K, directions(L), N))
