@@ -135,20 +135,20 @@ int bpc_decode_path_taken(int B, int Hq, int Hkv, int N, int L);
  *           decisions is ADDED (the caller zeroes it), or NULL
  * workspace    device memory of at least bpc_build_workspace_bytes(...)
  *           bytes, 256-byte aligned; its contents on entry do not matter.
- * Cost: 2 L + 4 kernel launches.  Nothing of size N x D is stored and no
- * residual is formed: with bpc_build_workspace_bytes(...) bytes each bit is one
- * pass over the bf16 keys, in which a_j and sum_j u_j R_j come from unrolled
- * sums, every sign and every entry of P certified to be the one the arithmetic
- * above gives, or computed in that arithmetic; the results are bit for bit
- * those.  The workspace then holds the codes as bit planes (L / 8 bytes per
- * key), 2 bytes per key and per-workgroup sums.  A smaller workspace, down to
- * one fp64 partial sum per 128-key chunk and coordinate plus fp64 copies of P
- * and G, is accepted as well: each pass then recomputes every R_j from the
- * key, its code bits so far and P, with the same results (as a call over at
- * most 40960 keys does on any workspace, being faster there).
- * bpc_build_checkpoint_workspace_bytes gives 1 KiB more per key (the size of
- * an fp64 residual, rounded up to 128-key chunks); it is accepted like any
- * larger workspace and no longer makes a difference.
+ * With bpc_build_workspace_bytes(...) bytes and many keys each bit is one pass
+ * over the bf16 keys, in which a_j and sum_j u_j R_j come from unrolled sums, every
+ * sign and every entry of P certified to be the one the arithmetic above gives,
+ * or computed in that arithmetic; the results are bit for bit those (2 L + 6
+ * kernel launches).  The workspace then holds the codes as bit planes (L / 8
+ * bytes per key), 2 bytes per key, one fp64 partial sum per 128-key chunk and
+ * coordinate (8 bytes per key) and per-workgroup sums.  Few keys, and a smaller
+ * workspace, down to those partial sums and fp64 copies of P and G, take passes
+ * that recompute every R_j from the key, its code bits so far and P (2 L + 2
+ * launches), with the same results.  Where those are the faster way,
+ * bpc_build_checkpoint_workspace_bytes asks for 1 KiB per key more, in which they
+ * keep each key's fp64 residual every 16 bits (up to 7 times as fast, over few
+ * keys per head); elsewhere it gives the same size as
+ * bpc_build_workspace_bytes.  A larger workspace is always accepted.
  */
 size_t bpc_build_workspace_bytes(int B, int Hkv, int N, int D, int L);
 size_t bpc_build_checkpoint_workspace_bytes(int B, int Hkv, int N, int D, int L);

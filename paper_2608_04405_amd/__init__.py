@@ -297,8 +297,9 @@ def build_hash(K: torch.Tensor, G: torch.Tensor, N: Optional[int] = None, *,
     when given, is a contiguous [B, Hkv, N] fp32 tensor.  When `fragile` (a
     1-element int64 GPU tensor) is given, the number of fragile sign
     decisions is added to it.  With `checkpoint` the workspace allocated
-    here is 1 KiB per key larger, which no longer makes a difference: the
-    results and the time are the same."""
+    here also holds, where that is the faster way (few keys), a checkpoint of
+    the fp64 residuals (1 KiB per key); a given workspace enables it by its
+    size alone.  Results are the same."""
     _need(K, "K", torch.bfloat16, 4)
     B, Hkv, Ncap, D = K.shape
     N = Ncap if N is None else N

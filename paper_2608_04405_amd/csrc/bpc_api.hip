@@ -126,6 +126,8 @@ BuildLayout build_layout(int B, int Hkv, int N, int L) {
   b.off_fold = take(BH * b.nfold * (size_t)kHeadDim * sizeof(double));  // and per block of chunks
   b.off_g64 = take((size_t)L * kHeadDim * sizeof(double));              // G widened to fp64
   b.total_min = o;
+  b.off_ck = take(BH * b.nchunks * (size_t)kBuildChunk * kHeadDim * sizeof(double));  // padded to whole chunks
+  b.total_ck = o;
 
   o = shared;
   b.off_sfold = take(BH * ((b.nchunks + kDenseFold - 1) / kDenseFold) * (size_t)kHeadDim * sizeof(double));
@@ -148,7 +150,6 @@ BuildLayout build_layout(int B, int Hkv, int N, int L) {
   b.off_tab = take(BH * (size_t)(L / 8) * 256 * sizeof(float));
   b.off_bound = take(BH * 4 * sizeof(float));
   b.total = o > b.total_min ? o : b.total_min;
-  b.total_ck = align_up(b.total + BH * b.nchunks * (size_t)kBuildChunk * kHeadDim * sizeof(double), 256);
   return b;
 }
 
@@ -205,7 +206,8 @@ size_t bpc_build_workspace_bytes(int B, int Hkv, int N, int D, int L) {
 
 size_t bpc_build_checkpoint_workspace_bytes(int B, int Hkv, int N, int D, int L) {
   if (B < 1 || Hkv < 1 || N < 1 || D != kHeadDim) return 0;
-  return build_layout(B, Hkv, N, L).total_ck;
+  const BuildLayout b = build_layout(B, Hkv, N, L);
+  return build_path(B, Hkv, N, L, true) == kBuildCheckpoint ? b.total + (b.total_ck - b.total_min) : b.total;
 }
 
 int bpc_build_hash(const uint16_t* K, int64_t sK_b, int64_t sK_h, int64_t sK_n, int B, int Hkv, int N,
@@ -229,7 +231,7 @@ int bpc_build_hash(const uint16_t* K, int64_t sK_b, int64_t sK_h, int64_t sK_n, 
   if (reinterpret_cast<uintptr_t>(workspace) & 255u) return fail(BPC_EALIGN, "workspace must be 256-byte aligned");
   const BuildArgs a{K, sK_b, sK_h, sK_n, B, Hkv, N, L, G, P_out, codes_out, sC_b, sC_h, err_out, fragile_out,
                     static_cast<char*>(workspace), static_cast<hipStream_t>(stream)};
-  hipError_t e = launch_build(a, workspace_bytes >= lay.total);
+  hipError_t e = launch_build(a, workspace_bytes);
   if (e != hipSuccess) return hip_fail(e, "bpc_build_hash launch");
   return BPC_OK;
 }

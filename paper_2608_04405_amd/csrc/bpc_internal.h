@@ -75,13 +75,14 @@ constexpr size_t kSyncRegionBytes = kSyncCounterBytes + (size_t)kFusedMaxBH * kF
 constexpr int kBuildGroups = 2;                  // groups of 64 keys per build workgroup
 constexpr int kBuildThreads = 256 * kBuildGroups;  // four wavefronts (coordinate blocks) per group
 constexpr int kBuildChunk = 64 * kBuildGroups;     // keys per workgroup (one chunk of the row tree)
+// bits between stored fp64 residuals when the build keeps a checkpoint
+constexpr int kBuildCkptPeriod = 16;
 // chunk sums folded per workgroup before the per-(b, h) reduction, when a
 // (b, h) has more than 8 such blocks of chunks
 constexpr int kBuildFold = 32;
 constexpr int kDenseFold = 16;  // and per round in a (b, h) that has left the scan
 // fp64 values per (b, h) and coordinate that the scanning build carries from bit to bit
 constexpr int kScanStats = 7;
-constexpr int kScanMinKeys = 40960;  // keys of the whole call up to which the rebuilding passes are faster
 constexpr int kScanWgs = 512;  // workgroups of one of its passes: two per compute unit, all resident
 
 // ---- workspace layouts -----------------------------------------------------
@@ -119,7 +120,8 @@ struct BuildLayout {
   int scan_wgs, scan_blocks;
   size_t off_psum, off_pcnt, off_node, off_planes, off_knorm, off_stat, off_cmat, off_corr, off_tab, off_bound,
       off_sfold, off_mode, total;
-  size_t total_ck;  // with the room of an fp64 residual per key, which no build needs any more
+  // the rebuilding passes with a checkpoint: an fp64 residual per key
+  size_t off_ck, total_ck;
 };
 
 // smallest: the smallest slice considered (more slices need more workspace)
@@ -233,8 +235,11 @@ struct BuildArgs {
   char* ws;
   hipStream_t stream;
 };
-// scan: the workspace holds BuildLayout::total bytes (else total_min)
-hipError_t launch_build(const BuildArgs& a, bool scan);
+enum BuildPath { kBuildPlain, kBuildCheckpoint, kBuildScan };
+// the fastest path of a call, with or without room for a checkpoint
+BuildPath build_path(int B, int Hkv, int N, int L, bool checkpoint);
+// ws_bytes: at least BuildLayout::total_min; what the path needs beyond decides too
+hipError_t launch_build(const BuildArgs& a, size_t ws_bytes);
 // the scanning build of P (and its fp64 widening) and the codes
 void launch_build_scan(const BuildArgs& a, const BuildLayout& lay);
 

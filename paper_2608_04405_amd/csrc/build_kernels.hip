@@ -17,10 +17,10 @@
 namespace bpc {
 
 // ============================================================================
-// Algorithm 1 in its own arithmetic, for workspaces too small for the scanning
-// build (build_scan_kernels.hip, which needs L / 8 + 2 bytes per key more or
-// less beside its sums, and rows below 32 MiB apart), and for the residual
-// norms after either.  Each bit is one pass over the keys of every (sequence,
+// Algorithm 1 in its own arithmetic, for few keys (build_path), for workspaces
+// too small for the scanning build (build_scan_kernels.hip, which needs some L / 8
+// + 2 bytes per key more, and rows below 32 MiB apart), and for the residual norms
+// after either.  Each bit is one pass over the keys of every (sequence,
 // KV head) plus one reduction per (b, h):
 //   build_bit_kernel    one workgroup per chunk of kBuildChunk keys, in groups
 //                       of 64 (one key per lane); the four wavefronts of a
@@ -45,9 +45,12 @@ namespace bpc {
 //                       v = s / N,
 //                       P[i] = (float)v (and its fp64 widening for the next
 //                       passes).
-// Nothing of size N x D is stored: the pass reads the keys again,
-// trading fp64 arithmetic (about L^2 D / 2 fused subtractions per key over the
-// whole build) for memory traffic.
+// Without a checkpoint nothing of size N x D is stored: the pass reads the keys
+// again, trading fp64 arithmetic (about L^2 D / 2 fused subtractions per key over
+// the whole build) for memory traffic.  With one (1 KiB per key of workspace), the
+// pass at every multiple m T of kBuildCkptPeriod also stores R after m T bits, in
+// place, and the passes up to (m + 1) T start from it: at most T subtractions per
+// pass, for a 1 KiB read instead of the 256-byte key.
 // ============================================================================
 
 __global__ void build_prep_kernel(const float* __restrict__ G, double* __restrict__ G64, int n) {
@@ -59,7 +62,8 @@ template <int W>
 __global__ __launch_bounds__(kBuildThreads) void build_bit_kernel(
     const uint16_t* __restrict__ K, int64_t sK_b, int64_t sK_h, int64_t sK_n, int Hkv, int N, int L, int bit,
     const double* __restrict__ G64, const double* __restrict__ P64, uint32_t* __restrict__ codes, int64_t sC_b,
-    int64_t sC_h, double* __restrict__ part, int nchunks, unsigned long long* __restrict__ fragile) {
+    int64_t sC_h, double* __restrict__ part, int nchunks, unsigned long long* __restrict__ fragile,
+    double* __restrict__ ck, int ck_from, int ck_store) {
   __shared__ double xch[kBuildGroups][4][64];         // per-block partial dots of each key
   __shared__ double groot[kBuildGroups][kHeadDim];    // tree root of each key group
   __shared__ int frag;
@@ -77,8 +81,24 @@ __global__ __launch_bounds__(kBuildThreads) void build_bit_kernel(
 #pragma unroll
   for (int w = 0; w < W; ++w) cw[w] = 0u;
   uint32_t* crow = codes + b * sC_b + h * sC_h + (int64_t)(valid ? key : 0) * W;
+  // this lane's 32 coordinates in the checkpoint: element e of the block at
+  // ckrow[(e / 2) * 64 + lane], so that each load covers 1 KiB of the
+  // wavefront's keys
+  typedef double f64x2 __attribute__((ext_vector_type(2)));
+  f64x2* ckrow = ck ? reinterpret_cast<f64x2*>(ck + ((((size_t)bh * nchunks + blockIdx.x) * kBuildGroups + grp) * 4 +
+                                                     c) * (32 * 64)) + lane
+                    : nullptr;
   if (valid) {
-    load_block(K + b * sK_b + h * sK_h + (int64_t)key * sK_n + 32 * c, r);
+    if (ck_from > 0) {
+#pragma unroll
+      for (int e2 = 0; e2 < 16; ++e2) {
+        const f64x2 x = __builtin_nontemporal_load(ckrow + 64 * e2);
+        r[2 * e2] = x.x;
+        r[2 * e2 + 1] = x.y;
+      }
+    } else {
+      load_block(K + b * sK_b + h * sK_h + (int64_t)key * sK_n + 32 * c, r);
+    }
 #pragma unroll
     for (int w = 0; w < W; ++w)
       if (32 * w < bit) cw[w] = crow[w];
@@ -86,8 +106,16 @@ __global__ __launch_bounds__(kBuildThreads) void build_bit_kernel(
 #pragma unroll
     for (int e = 0; e < 32; ++e) r[e] = 0.0;  // never contributes: padded below
   }
-  // the residual after bits 0 .. bit - 1
-  remove_bits<W>(r, cw, bit, uniform_ptr(P64 + (size_t)bh * L * kHeadDim + 32 * c));
+  // the residual after bits 0 .. bit - 1: bits ck_from .. bit - 1 removed from
+  // the checkpoint (or all of them from the key)
+  remove_bits<W>(r, cw, ck_from, bit, uniform_ptr(P64 + (size_t)bh * L * kHeadDim + 32 * c));
+  if (ck_store && valid) {
+#pragma unroll
+    for (int e2 = 0; e2 < 16; ++e2) {
+      const f64x2 x = {r[2 * e2], r[2 * e2 + 1]};
+      __builtin_nontemporal_store(x, ckrow + 64 * e2);
+    }
+  }
   // a_j = R_j . g (four blocks of 32, ascending, combined ((b0 + b1) + (b2 + b3)))
   const_ptr<double> g = uniform_ptr(G64 + (size_t)bit * kHeadDim + 32 * c);
   double acc = 0.0;
@@ -194,21 +222,25 @@ __global__ __launch_bounds__(kFinishBlocks* kHeadDim) void build_finish_kernel(i
 }
 
 template <int W>
-static void launch_build_W(const BuildArgs& a, const BuildLayout& lay, bool scan) {
+static void launch_rebuild(const BuildArgs& a, const BuildLayout& lay, bool checkpoint) {
   double* part = reinterpret_cast<double*>(a.ws + lay.off_part);
   double* fold = reinterpret_cast<double*>(a.ws + lay.off_fold);
   double* P64 = reinterpret_cast<double*>(a.ws + lay.off_p64);
   double* G64 = reinterpret_cast<double*>(a.ws + lay.off_g64);
   const int BH = a.B * a.Hkv;
   const dim3 grid(lay.nchunks, BH);
-  if (!scan) {
-    const int ng = a.L * kHeadDim;
-    build_prep_kernel<<<(ng + 255) / 256, 256, 0, a.stream>>>(a.G, G64, ng);
-  }
-  for (int bit = 0; bit < a.L && !scan; ++bit) {
+  double* ck = checkpoint ? reinterpret_cast<double*>(a.ws + lay.off_ck) : nullptr;
+  const int ng = a.L * kHeadDim;
+  build_prep_kernel<<<(ng + 255) / 256, 256, 0, a.stream>>>(a.G, G64, ng);
+  for (int bit = 0; bit < a.L; ++bit) {
+    // With a checkpoint the pass at bit m T stores R after m T bits, and the
+    // passes up to the next one start from it.
+    const int past = bit % kBuildCkptPeriod;
+    const int from = ck ? max(bit - (past ? past : kBuildCkptPeriod), 0) : 0;
+    const int store = ck && bit > 0 && past == 0;
     build_bit_kernel<W><<<grid, kBuildThreads, 0, a.stream>>>(a.K, a.sK_b, a.sK_h, a.sK_n, a.Hkv, a.N, a.L, bit, G64,
                                                              P64, a.codes, a.sC_b, a.sC_h, part, lay.nchunks,
-                                                             a.fragile);
+                                                             a.fragile, ck, from, store);
     if (lay.nfold) {
       build_fold_kernel<<<dim3(lay.nfold, BH), kHeadDim, 0, a.stream>>>(part, lay.nchunks, fold, lay.nfold);
       build_finish_kernel<<<BH, kFinishBlocks * kHeadDim, 0, a.stream>>>(a.N, a.L, bit, lay.nfold, fold, a.P, P64);
@@ -218,18 +250,61 @@ static void launch_build_W(const BuildArgs& a, const BuildLayout& lay, bool scan
   }
 }
 
-hipError_t launch_build(const BuildArgs& a, bool scan) {
+// Scan (S), rebuilding passes (R) or those with a checkpoint (C), by the time of
+// the whole build.  The rebuilding passes hold one 128-key chunk per compute unit
+// up to 256 chunks and take little more for 256 than for one, but reduce the
+// chunks of a (b, h) in one workgroup (up to 256 of them; beyond, folded first);
+// the scan has two launches per bit of some 10 us, handles 256 keys of a (b, h)
+// per workgroup, and over no more keys than bits leaves itself for dense_pass.
+// Measured ratios:
+//   S / R up to 256 chunks: L = 32, one head of 4096, 8192 and 32768 keys 1.04,
+//     0.88, 0.49, 2 x 4096 and 6144 1.04, 0.92, 8 x 4096 1.05; L = 64, one of 2048
+//     and 4096 1.03, 0.98, 8 x 2048 and 3072 1.00, 0.95, 32 x 1024 1.04; L = 128
+//     0.85 to 1.0 beyond 128 keys, 2 to 3.2 up to 128.
+//   S / R beyond: 0.25 to 0.94; but L = 32, one head of 65536, 98304, 131072 keys
+//     1.24, 1.08, 1.01, and up to 128 keys per head 1.05 to 1.25 at L = 32 (0.8 to 0.9
+//     at L = 64, 2 to 3.7 at 128).
+//   S / C up to 256 chunks: one head of 8192 and 12288 keys 0.96, 0.76 (L = 32), 1.00,
+//     0.82 (64), 1.22, 0.98 (128), 2 x 6144 0.99, 1.05, 1.27; 8 x 4096 1.07, 1.11, 1.42.
+//   S / C beyond: up to 128 keys per head 1.3 to 3.7; one head of 49152, 98304, 131072
+//     1.05, 1.07, 0.99 (32), 1.04, 0.99, 0.91 (64), 1.28, 1.18, 0.96 (128); L = 64, 128
+//     heads, 49152 and 65536 keys in all 1.04, 0.96, 8 heads 0.81, 0.73; L = 128, 16 heads, 65536
+//     and 98304 1.13, 0.87, 8 heads, 49152 and 65536 1.01, 0.91, 512 heads x 256 1.25.
+BuildPath build_path(int B, int Hkv, int N, int L, bool checkpoint) {
+  const int64_t BH = (int64_t)B * Hkv, keys = BH * N;
+  const int64_t chunks = BH * ((N + kBuildChunk - 1) / kBuildChunk);
+  const bool few = chunks <= 256;
+  bool scan;
+  if (!checkpoint) {
+    if (N <= kBuildChunk) scan = L == 64 && !few;
+    else if (few) scan = (int64_t)N * L >= 6144 * 32;
+    else scan = !(L == 32 && BH == 1 && N < 196608);
+    return scan ? kBuildScan : kBuildPlain;
+  }
+  if (few) scan = N >= (L == 32 ? 6144 : L == 64 ? 8192 : 12288);
+  else if (N <= kBuildChunk) scan = false;
+  else if (BH == 1) scan = N >= (L == 64 ? 98304 : 131072);
+  else if (L == 32) scan = true;
+  else if (L == 64) scan = BH <= 64 || keys >= 65536;
+  else scan = (N >= 12288 && N <= 32768) || (N > 256 && keys >= (BH <= 8 ? 65536 : 98304));
+  return scan ? kBuildScan : kBuildCheckpoint;
+}
+
+hipError_t launch_build(const BuildArgs& a, size_t ws_bytes) {
   const BuildLayout lay = build_layout(a.B, a.Hkv, a.N, a.L);
-  // The scan's tiles of 64 rows are addressed by 32-bit offsets.  Over few keys
-  // its two dependent launches per bit cost more than rebuilding the residuals
-  // (8 x 4096 keys, scan against rebuild: L = 32 474 and 457 us, L = 64 1155 and
-  // 1081, L = 128 3894 and 2918; 8 x 8192, L = 64: 1295 and 1675).
-  scan = scan && a.sK_n < (1 << 24) && (int64_t)a.B * a.Hkv * a.N > kScanMinKeys;
-  if (scan) launch_build_scan(a, lay);
-  switch (a.L) {
-    case 32: launch_build_W<1>(a, lay, scan); break;
-    case 64: launch_build_W<2>(a, lay, scan); break;
-    default: launch_build_W<4>(a, lay, scan); break;
+  const bool room = ws_bytes >= lay.total_ck;
+  BuildPath path = build_path(a.B, a.Hkv, a.N, a.L, room);
+  // (the scan's tiles of 64 rows are addressed by 32-bit offsets)
+  if (path == kBuildScan && (ws_bytes < lay.total || a.sK_n >= (1 << 24)))
+    path = room ? kBuildCheckpoint : kBuildPlain;
+  if (path == kBuildScan) {
+    launch_build_scan(a, lay);
+  } else {
+    switch (a.L) {
+      case 32: launch_rebuild<1>(a, lay, path == kBuildCheckpoint); break;
+      case 64: launch_rebuild<2>(a, lay, path == kBuildCheckpoint); break;
+      default: launch_rebuild<4>(a, lay, path == kBuildCheckpoint); break;
+    }
   }
   if (a.err)
     return launch_norm(a.K, a.sK_b, a.sK_h, a.sK_n, a.B, a.Hkv, a.N, a.L, a.P, (int64_t)a.Hkv * a.L * kHeadDim,

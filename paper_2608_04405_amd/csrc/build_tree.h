@@ -57,15 +57,16 @@ __device__ __forceinline__ void load_block(const uint16_t* krow, double (&r)[32]
   }
 }
 
-// the residual after bits 0 .. bit - 1, whose signs are cw; prow: this block's
-// coordinates of P
+// bits from .. bit - 1, whose signs are in cw, removed from the residual; prow:
+// this block's coordinates of P
 template <int W>
-__device__ __forceinline__ void remove_bits(double (&r)[32], const uint32_t* cw, int bit, const_ptr<double> prow) {
+__device__ __forceinline__ void remove_bits(double (&r)[32], const uint32_t* cw, int from, int bit,
+                                            const_ptr<double> prow) {
 #pragma unroll
   for (int w = 0; w < W; ++w) {
     const int nb = min(32, bit - 32 * w);
     const uint32_t word = cw[w];
-    for (int ib = 0; ib < nb; ++ib) {
+    for (int ib = max(0, from - 32 * w); ib < nb; ++ib) {
       const double sg = ((word >> ib) & 1u) ? -1.0 : 1.0;
       const_ptr<double> p = prow + (size_t)(32 * w + ib) * kHeadDim;
 #pragma unroll

@@ -80,9 +80,11 @@ def directions(L, seed=1):
 # one key; one short, one whole, one whole and a bit 64-key tile; a 128-key
 # chunk and a bit; a wavefront's and a workgroup's share and a bit; more than
 # one block per wavefront
-# (more than 40960 keys in all, below which the rebuilding passes run anyway)
-@pytest.mark.parametrize("L,N,B,H", [(32, 1, 8, 5200), (64, 63, 8, 96), (64, 64, 8, 96), (128, 65, 8, 96),
-                                     (32, 129, 8, 48), (64, 257, 8, 24), (128, 1025, 8, 8), (64, 40961, 1, 8)])
+# (more than 256 chunks in all, or long heads, below which the rebuilding passes
+# run anyway, as they do up to 128 keys per head but for L = 64)
+@pytest.mark.parametrize("L,N,B,H", [(32, 1, 8, 5200), (64, 1, 8, 5200), (64, 63, 8, 96), (64, 64, 8, 96),
+                                     (64, 65, 8, 96), (128, 65, 8, 96), (128, 129, 8, 96), (32, 129, 8, 48),
+                                     (64, 257, 8, 24), (128, 1025, 8, 8), (64, 40961, 1, 8), (32, 6150, 1, 2)])
 def test_sizes(L, N, B, H):
     print(f"[build scan] L={L} N={N} B={B} H={H}", flush=True)
     assert_same(both(keys(N, B, H, seed=N), directions(L), N, codes_stride_rows=3))
@@ -160,7 +162,7 @@ def test_sign_of_a_vanished_column(L):
 # residuals, one bit behind the others: few different keys, a NaN, every sign
 # uncertain, beside heads that go on scanning; one chunk, one fold of chunks and
 # several, whole and ragged.
-@pytest.mark.parametrize("L,N,H", [(32, 100, 420), (64, 643, 72), (128, 640, 72), (64, 2049, 24), (32, 5000, 12),
+@pytest.mark.parametrize("L,N,H", [(64, 100, 420), (64, 643, 72), (128, 640, 72), (64, 2049, 24), (32, 5000, 12),
                                    (64, 70001, 3)])
 @pytest.mark.parametrize("form", ["two_keys", "few_keys", "nan", "negative_zeros", "rank_one"])
 def test_leaving_the_scan(form, L, N, H):
@@ -180,3 +182,26 @@ def test_leaving_the_scan(form, L, N, H):
     elif form == "rank_one":
         part[:] = (part[:, :, :1].float() * torch.randint(-3, 4, (1, 1, N, 1), device=DEV)).to(torch.bfloat16)
     assert_same(both(K, directions(L), N))
+
+
+# either side of the bounds between the scan, the rebuilding passes and those
+# with a checkpoint
+@pytest.mark.parametrize("L,N,H", [(32, 6143, 1), (32, 6144, 1), (64, 3071, 2), (64, 3072, 2), (64, 8192, 1),
+                                   (128, 1535, 4), (128, 1536, 4), (128, 12288, 1), (64, 128, 256), (64, 128, 257),
+                                   (128, 128, 257), (128, 129, 129), (32, 256, 129), (128, 1000, 70),
+                                   (64, 600, 70), (64, 1000, 70)])
+def test_paths(L, N, H):
+    """Three sizes of workspace: the same results, whichever path each takes."""
+    print(f"[build scan] paths L={L} N={N} H={H}", flush=True)
+    K, G = keys(N, H=H, seed=L + N), directions(L)
+    sizes = {small_workspace(1, H, N, L), small_workspace(1, H, N, L) + 1024 * 128 * H * -(-N // 128),
+             bpc.build_workspace_bytes(1, H, N, L), bpc.build_checkpoint_workspace_bytes(1, H, N, L)}
+    res = []
+    for size in sorted(sizes):
+        ws = torch.randint(0, 256, (size,), dtype=torch.uint8, device=DEV)
+        err = torch.empty(1, H, N, device=DEV)
+        frag = torch.zeros(1, dtype=torch.int64, device=DEV)
+        P, codes, err = bpc.build_hash(K, G, err_out=err, fragile=frag, workspace=ws)
+        res.append((P, codes, err, int(frag)))
+    for r in res[1:]:
+        assert_same((res[0], r))
