@@ -2865,8 +2865,11 @@ int decode_fused_slice(int B, int Hq, int Hkv, int N, int L, int smallest) {
   // keys, L = 32: 24.8 -> 17.6 us).  Slices of 2048 pay while a (b, h) has at
   // most 16 of them and the grid at most one workgroup per compute unit
   // (against 4096: 1 x 8 heads x 4096 keys, L = 64, 20.7 -> 18.2 us; x 32768
-  // 21.7 -> 20.5; 4 x 8 x 16384 23.0 -> 20.3; beyond 16 the exchange between
-  // the slices costs more than they save: 1 x 8 x 131072 27.0 -> 33.4).
+  // 21.7 -> 20.5; 4 x 8 x 16384 23.0 -> 20.3).  Beyond 16 the exchange between the
+  // slices takes up what they save (4096 against 2048 keys, L = 64, four query
+  // heads per KV head: 4 x 40960 keys 21.5 and 20.5 us, 4 x 49152 21.7 and 21.3, 8 x
+  // 49152 22.0 and 22.2, 8 x 65536 22.5 and 22.9, 2 x 98304 23.7 and 24.2; eight:
+  // 8 x 49152 25.2 and 26.7; L = 32, one: 4 x 98304 20.1 and 22.4).
   if (path == 0 && small_slices_built(L, G)) {
     const int64_t ncu = device_cu_count();
     for (const int sl : {kSliceTiny, kSliceSmall, kSliceMid}) {

@@ -3,6 +3,8 @@ certified rows of P) against the build that rebuilds every residual in the
 reference arithmetic, which runs on a workspace too small for the former: the
 same P, codes, errors and fragile counts bit for bit.  (Both are checked
 against the oracle in test_gpu_parity.py and test_gpu_fullsize.py.)"""
+import math
+
 import numpy as np
 import pytest
 import torch
@@ -128,15 +130,50 @@ def test_forms(form, L):
     assert_same(both(K, directions(L), N if form != "strided" else N - 57))
 
 
-def test_many_uncertified_columns():
-    """Directions in which the residual's sum is far below its terms: P rows
-    near rounding boundaries of a coarse grid, so that columns are summed again
-    in the reference order."""
+def test_small_integers():
+    """Sums that are exact and often lie halfway between two floats, which is
+    where a bound other than zero would not certify them."""
     N, L = 2048, 64
     g = torch.Generator(device=DEV).manual_seed(3)
     K = torch.randint(-4, 5, (1, 24, N, 128), generator=g, device=DEV).to(torch.bfloat16)
     K[:, :, ::2] = -K[:, :, 1::2]
     assert_same(both(K, directions(L), N))
+
+
+def test_uncertified_columns():
+    """Columns that cannot certify, few enough for the scan to go on: the sum of
+    u_j R_jd cancels while its terms span more than 53 bits, so that nothing is
+    known of its sign.  Three cancel at the first bit, three at the second (with
+    the first row of P removed); 27 chunks, the last of four keys."""
+    N, L = 26 * 128 + 4, 64
+    rng = np.random.default_rng(8)
+    u0, u1 = np.array([[1, 1], [1, -1], [-1, 1], [-1, -1]] * (N // 4)).T[:, rng.permutation(N)]
+    to = lambda x: torch.from_numpy(np.ascontiguousarray(x)).float().to(torch.bfloat16)
+    K = keys(N, H=2, seed=9).cpu()
+    K[..., 0], K[..., 1] = to(u0 * rng.uniform(1, 2, N)), to(u1 * rng.uniform(1, 2, N))
+    for d in (10, 11, 12, 20, 21, 22):
+        x = to(2.0 ** rng.uniform(-60, 0, N // 2)).float().numpy().astype(np.float64)
+        x[0], x[1] = 1.0, 2.0 ** -60
+        k = np.zeros(N)
+        if d < 20:  # pairs of one u0, opposite values
+            order = np.concatenate([rng.permutation(np.flatnonzero(u0 == s)) for s in (1, -1)])
+        else:       # pairs of one u1 and both u0: the sum of u0 k does not cancel
+            order = np.stack([np.concatenate([rng.permutation(np.flatnonzero((u1 == s) & (u0 == t))) for s in (1, -1)])
+                              for t in (1, -1)], 1).reshape(-1)
+        k[order[::2]], k[order[1::2]] = x, -x
+        u = u0 if d < 20 else u1
+        # what the certificate needs does not hold: the sum is 0 (with equally
+        # many u0 = u1 and u0 = -u1 also after the first bit) and cannot be exact
+        assert math.fsum(u * k) == 0.0 and (u0 * u1).sum() == 0
+        assert N * np.abs(k).max() >= 2.0 ** 53 * np.abs(k).min() * 2.0 ** -7
+        assert d < 20 or math.fsum(u0 * k) > 1.0
+        K[..., d] = to(k)
+    G = directions(L)
+    G[:2] = 0
+    G[0, 0], G[1, 1] = 1.0, 1.0
+    res = both(K.to(DEV), G, N)
+    assert_same(res)
+    assert_same((res[0], by_oracle(K, G, N)))
 
 
 @pytest.mark.parametrize("L", [32, 64, 128])

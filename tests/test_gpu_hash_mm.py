@@ -174,15 +174,22 @@ def test_mm_large_and_tiny_projection():
 
 
 def test_mm_matches_canonical_kernel_on_a_large_batch():
-    """Consistency over many keys: the matrix-core codes equal those of the
-    fixed-order fp64 kernel (itself checked against the oracle) on one
-    workload layer of 8 x 8 heads x 65536 keys; the fragile counts agree."""
+    """Consistency over many keys: the codes of hash_keys_mm and hash_keys equal
+    those of the fixed-order fp64 kernel (that of append, itself checked against
+    the oracle) on one workload layer of 8 x 8 heads x 65536 keys; the fragile
+    counts agree, and the norms of hash_keys are that kernel's."""
     cfg = config_by_name("stack32_b8_64k")
     d = make_layer(cfg, device=DEV)
-    P, _, _ = bpc.build_hash(d["K"], d["G"].to(DEV))
-    f1 = torch.zeros(1, dtype=torch.int64, device=DEV)
-    c1, _ = bpc.hash_keys(d["K"], P, fragile=f1)
-    c2, f2, fall = run_mm(d["K"], P)
-    assert torch.equal(c1, c2)
-    assert int(f1.item()) == f2
+    K = d["K"]
+    P, _, _ = bpc.build_hash(K, d["G"].to(DEV))
+    Kc, Vc = torch.empty_like(K), torch.empty_like(K)
+    c1 = torch.zeros(*K.shape[:3], P.shape[2] // 32, dtype=torch.int32, device=DEV)
+    e1, e3 = torch.empty(K.shape[:3], device=DEV), torch.empty(K.shape[:3], device=DEV)
+    f1, f3 = torch.zeros(1, dtype=torch.int64, device=DEV), torch.zeros(1, dtype=torch.int64, device=DEV)
+    bpc.append_kv(K, K, Kc, Vc, c1, P, 0, err_out=e1, fragile=f1)
+    assert torch.equal(Kc, K) and torch.equal(Vc, K)
+    c2, f2, fall = run_mm(K, P)
+    c3, _ = bpc.hash_keys(K, P, err_out=e3, fragile=f3)
+    assert torch.equal(c1, c2) and torch.equal(c1, c3) and torch.equal(e1, e3)
+    assert int(f1.item()) == f2 == int(f3.item())
     announce(f"stack layer 0: {cfg.B * cfg.Hkv * cfg.N} keys equal, {f2} fragile, {fall} recomputed")
