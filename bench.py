@@ -58,8 +58,8 @@ def parse():
                     help="summarize rocprofv3 csv output under each DIR (kernel stats and counters per dispatch) "
                          "instead of benchmarking")
     ap.add_argument("--prefill-only", metavar="WORKLOAD", default=None,
-                    help="time only the prefill of one layer of WORKLOAD: Algorithm 1 on either size of "
-                         "workspace, then Algorithm 2 by both entry points; print one JSON line")
+                    help="time only the prefill of one layer of WORKLOAD: Algorithm 1, then Algorithm 2 by "
+                         "both entry points; print one JSON line")
     ap.add_argument("--pmc-json", metavar="PATH", default=None,
                     help="with --summarize over a FETCH_SIZE and a WRITE_SIZE run: write HBM bytes per launch")
     return ap.parse_args()
@@ -83,9 +83,9 @@ def source_sha() -> str:
 
 
 def _build_passes(path, root):
-    """The Algorithm 1 builds of a kernel trace, one line each: the passes
-    (build_bit launches, one per bit and a last one for the errors) and the
-    time of the bit passes by range of bits."""
+    """The Algorithm 1 builds of a kernel trace, one line each: the passes over
+    the keys (one launch per bit, one more where the scan may have to repeat a
+    bit) by range of bits, and the launches between them."""
     import csv
     rows = []
     for r in csv.DictReader(open(path)):
@@ -95,22 +95,24 @@ def _build_passes(path, root):
     rows.sort()
     builds, cur = [], None
     for t0, t1, n in rows:
-        if "build_prep" in n:
-            cur = {"bit": [], "finish": [], "t0": t0, "t1": t1}
+        if "build_prep" in n or "build_stat" in n:
+            cur = {"kind": "scanning" if "build_stat" in n else "rebuilding", "bit": [], "rest": [], "t0": t0, "t1": t1}
             builds.append(cur)
         elif cur is not None:
-            cur["bit" if "build_bit" in n else "finish"].append((t1 - t0) / 1e3)
+            cur["bit" if "build_bit" in n or "build_sign" in n else "rest"].append((t1 - t0) / 1e3)
             cur["t1"] = t1
     out = []
     if builds:
         out.append(f"Algorithm 1 builds ({os.path.relpath(path, root)}), durations in us:")
     for i, b in enumerate(builds):
-        bit = b["bit"]
+        bit, rest = b["bit"], b["rest"]
         nb = len(bit)
-        rng = [(a, min(e, nb - 1)) for a, e in ((0, 16), (16, 32), (32, 64), (64, nb - 1))] + [(nb - 1, nb)]
+        rng = [(a, min(e, nb)) for a, e in ((0, 16), (16, 32), (32, 64), (64, 128), (128, nb))]
         parts = ", ".join(f"passes {a}-{e - 1}: mean {sum(bit[a:e]) / (e - a):.1f}" for a, e in rng if e > a)
-        out.append(f"  build {i}: {len(bit)} bit passes, {sum(bit) / 1e3:.2f} ms in them, {sum(b['finish']) / 1e3:.2f} ms "
-                   f"in {len(b['finish'])} fold and finish launches, {(b['t1'] - b['t0']) / 1e6:.2f} ms first to last; {parts}")
+        mid = sorted(rest)[len(rest) // 2] if rest else 0.0
+        out.append(f"  build {i} ({b['kind']}): {nb} passes, {sum(bit) / 1e3:.2f} ms in them, {sum(rest) / 1e3:.2f} ms "
+                   f"in {len(rest)} other launches (median {mid:.1f}, longest {max(rest, default=0.0):.1f}), "
+                   f"{(b['t1'] - b['t0']) / 1e6:.2f} ms first to last; {parts}")
     return out
 
 
@@ -259,40 +261,30 @@ def measure_config(bpc, cfg, dev, n_inst, steps, warmup, log_name):
     frag = torch.zeros(1, dtype=torch.int64, device=dev)
     fall = torch.zeros(1, dtype=torch.int64, device=dev)
     ws_build = torch.empty(bpc.build_workspace_bytes(B, Hkv, N, L), dtype=torch.uint8, device=dev)
-    ws_ck = torch.empty(bpc.build_checkpoint_workspace_bytes(B, Hkv, N, L), dtype=torch.uint8, device=dev)
-    build_ms = build_ck_ms = hash_ms = hash_mm_ms = 0.0
+    build_ms = hash_ms = hash_mm_ms = 0.0
     data = []
     t0 = time.time()
     for i in range(n_data):
         d = make_layer(cfg, layer=i, device=dev)
-        ev = [torch.cuda.Event(enable_timing=True) for _ in range(5)]
+        ev = [torch.cuda.Event(enable_timing=True) for _ in range(4)]
         ev[0].record()
         P, codes, _ = bpc.build_hash(d["K"], d["G"].to(dev), fragile=frag if i == 0 or layers > 1 else None,
                                      workspace=ws_build)
         ev[1].record()
         if i == 0 or layers > 1:
-            c2, _ = bpc.hash_keys(d["K"], P)
+            bpc.hash_keys(d["K"], P)
         ev[2].record()
         if i == 0 or layers > 1:
-            c3 = bpc.hash_keys_mm(d["K"], P, fallbacks=fall)
+            bpc.hash_keys_mm(d["K"], P, fallbacks=fall)
         ev[3].record()
-        if i == 0 or layers > 1:
-            P4, c4, _ = bpc.build_hash(d["K"], d["G"].to(dev), workspace=ws_ck)
-        ev[4].record()
         torch.cuda.synchronize()
         if i == 0 or layers > 1:
             build_ms += ev[0].elapsed_time(ev[1])
             hash_ms += ev[1].elapsed_time(ev[2])
             hash_mm_ms += ev[2].elapsed_time(ev[3])
-            build_ck_ms += ev[3].elapsed_time(ev[4])
-            if not torch.equal(c2, c3):
-                raise RuntimeError(f"{log_name}: the two entry points of Algorithm 2 give different codes")
-            if not (torch.equal(P4, P) and torch.equal(c4, codes)):
-                raise RuntimeError(f"{log_name}: the Algorithm 1 builds on the two workspaces differ")
-            del c2, c3, P4, c4
         data.append({"q": d["q"], "K": d["K"], "V": d["V"], "codes": codes, "P": P})
         del d
-    del ws_build, ws_ck
+    del ws_build
     torch.cuda.empty_cache()
     keys_pf = B * Hkv * N * (layers if layers > 1 else 1)
     log(f"{log_name}: {n_data} layers/instances generated and built in {time.time() - t0:.1f}s")
@@ -322,7 +314,6 @@ def measure_config(bpc, cfg, dev, n_inst, steps, warmup, log_name):
            "slice_keys": bpc.decode_slice_keys(B, Hq, Hkv, N, L),
            "prefill": {"build_ms": round(build_ms, 2), "hash_ms": round(hash_ms, 2),
                        "build_keys_per_s": keys_pf / (build_ms * 1e-3), "hash_keys_per_s": keys_pf / (hash_ms * 1e-3),
-                       "build_checkpoint_ms": round(build_ck_ms, 2),
                        "hash_mm_ms": round(hash_mm_ms, 2), "hash_mm_keys_per_s": keys_pf / (hash_mm_ms * 1e-3),
                        "hash_mm_recomputed_decisions": int(fall.item()),
                        "fragile_sign_decisions": int(frag.item()),
@@ -348,9 +339,8 @@ def copy_ceiling(dev):
 
 
 def prefill_only(name):
-    """Prefill of one layer of a workload, each kernel path once after a
-    warm-up build: Algorithm 1 on the default and on the larger workspace
-    (results compared), Algorithm 2 by both entry points (codes compared)."""
+    """Prefill of one layer of a workload, each call once after a warm-up
+    build: Algorithm 1, Algorithm 2 by both entry points."""
     import torch
 
     import paper_2608_04405_amd as bpc
@@ -361,27 +351,23 @@ def prefill_only(name):
     d = make_layer(cfg, layer=0, device=dev)
     K, G = d["K"], d["G"].to(dev)
     del d
-    ws = torch.empty(bpc.build_checkpoint_workspace_bytes(B, Hkv, N, L), dtype=torch.uint8, device=dev)
-    small = ws[:bpc.build_workspace_bytes(B, Hkv, N, L)]
-    bpc.build_hash(K, G, workspace=small)  # warm-up
+    ws = torch.empty(bpc.build_workspace_bytes(B, Hkv, N, L), dtype=torch.uint8, device=dev)
+    err = torch.empty(B, Hkv, N, dtype=torch.float32, device=dev)
+    bpc.build_hash(K, G, err_out=err, workspace=ws)  # warm-up
     torch.cuda.synchronize()
-    ev = [torch.cuda.Event(enable_timing=True) for _ in range(5)]
+    ev = [torch.cuda.Event(enable_timing=True) for _ in range(4)]
     ev[0].record()
-    P1, c1, _ = bpc.build_hash(K, G, workspace=small)
+    P, _, _ = bpc.build_hash(K, G, err_out=err, workspace=ws)
     ev[1].record()
-    P2, c2, _ = bpc.build_hash(K, G, workspace=ws)
+    bpc.hash_keys(K, P, err_out=err)
     ev[2].record()
-    h1, _ = bpc.hash_keys(K, P1)
+    bpc.hash_keys_mm(K, P)
     ev[3].record()
-    h2 = bpc.hash_keys_mm(K, P1)
-    ev[4].record()
     torch.cuda.synchronize()
-    if not (torch.equal(P1, P2) and torch.equal(c1, c2) and torch.equal(h1, h2)):
-        raise RuntimeError(f"{name}: the prefill paths disagree")
-    t = [ev[i].elapsed_time(ev[i + 1]) for i in range(4)]
+    t = [ev[i].elapsed_time(ev[i + 1]) for i in range(3)]
     print(json.dumps({"workload": name, "keys": B * Hkv * N, "L": L, "build_ms": round(t[0], 3),
-                      "build_checkpoint_ms": round(t[1], 3), "hash_ms": round(t[2], 3), "hash_mm_ms": round(t[3], 3),
-                      "checkpoint_workspace_bytes": int(ws.numel())}), flush=True)
+                      "hash_ms": round(t[1], 3), "hash_mm_ms": round(t[2], 3),
+                      "workspace_bytes": int(ws.numel())}), flush=True)
 
 
 def main():
@@ -425,7 +411,6 @@ def main():
     prefill = {}
     frag = torch.zeros(1, dtype=torch.int64, device=dev)
     frag2 = torch.zeros(1, dtype=torch.int64, device=dev)
-    frag3 = torch.zeros(1, dtype=torch.int64, device=dev)
     fall3 = torch.zeros(1, dtype=torch.int64, device=dev)
     for i, it in enumerate(insts):
         ev = [torch.cuda.Event(enable_timing=True) for _ in range(5)]
@@ -436,21 +421,12 @@ def main():
         ev[1].record()
         if i == 0 and not args.no_prefill:
             err2 = torch.empty(B, Hkv, N, dtype=torch.float32, device=dev)
-            codes2, _ = bpc.hash_keys(it["K"], P, err_out=err2, fragile=frag2)
+            bpc.hash_keys(it["K"], P, err_out=err2, fragile=frag2)
             ev[2].record()
-            codes3 = bpc.hash_keys_mm(it["K"], P, fragile=frag3, fallbacks=fall3)
+            bpc.hash_keys_mm(it["K"], P, fallbacks=fall3)
             ev[3].record()
-            codes4, _ = bpc.hash_keys(it["K"], P)
+            bpc.hash_keys(it["K"], P)
             ev[4].record()
-            # Algorithm 1 again, on the larger workspace
-            del ws_build
-            ws_ck = torch.empty(bpc.build_checkpoint_workspace_bytes(B, Hkv, N, L), dtype=torch.uint8, device=dev)
-            err5 = torch.empty(B, Hkv, N, dtype=torch.float32, device=dev)
-            frag5 = torch.zeros(1, dtype=torch.int64, device=dev)
-            ev5 = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
-            ev5[0].record()
-            P5, codes5, _ = bpc.build_hash(it["K"], it["G"], err_out=err5, fragile=frag5, workspace=ws_ck)
-            ev5[1].record()
         torch.cuda.synchronize()
         it["P"], it["codes"], it["err"] = P, codes, err
         if i == 0 and not args.no_prefill:
@@ -458,31 +434,20 @@ def main():
             hash_ms = ev[1].elapsed_time(ev[2])
             hash_mm_ms = ev[2].elapsed_time(ev[3])
             hash_codes_ms = ev[3].elapsed_time(ev[4])
-            build_ck_ms = ev5[0].elapsed_time(ev5[1])
-            if not (torch.equal(codes2, codes3) and torch.equal(codes2, codes4)) or int(frag2.item()) != int(frag3.item()):
-                raise RuntimeError("the two entry points of Algorithm 2 differ")
-            if not (torch.equal(P5, P) and torch.equal(codes5, codes) and torch.equal(err5, err)
-                    and int(frag5.item()) == int(frag.item())):
-                raise RuntimeError("the Algorithm 1 builds on the two workspaces differ")
             keys = B * Hkv * N
             prefill = {"build_ms": round(build_ms, 3), "hash_ms": round(hash_ms, 3),
                        "build_keys_per_s": keys / (build_ms / 1e3), "hash_keys_per_s": keys / (hash_ms / 1e3),
-                       "build_checkpoint_ms": round(build_ck_ms, 3),
-                       "build_checkpoint_workspace_bytes": int(ws_ck.numel()),
                        "hash_codes_only_ms": round(hash_codes_ms, 3),
                        "hash_mm_ms": round(hash_mm_ms, 3), "hash_mm_keys_per_s": keys / (hash_mm_ms / 1e3),
-                       "hash_mm_speedup": round(hash_codes_ms / hash_mm_ms, 2),
                        "hash_mm_recomputed_decisions": int(fall3.item()),
                        "fragile_sign_decisions_build": int(frag.item()),
                        "fragile_sign_decisions_hash": int(frag2.item()),
                        "what": "Algorithm 1 (build P, codes and errors) and Algorithm 2 (hash every key, with "
                                "errors) for the whole batch, the results of the fp64 fixed-order arithmetic; "
-                               "build_checkpoint: the same build on the larger workspace; hash_codes_only: Algorithm 2 "
-                               "without the errors; hash_mm: the same codes by bpc_hash_keys_mm "
+                               "hash_codes_only: Algorithm 2 without the errors; hash_mm: the same codes by bpc_hash_keys_mm "
                                "(recomputed = decisions redone in fp64); fragile = "
                                "sign decisions with |a| < 1e-6"}
-            del codes2, codes3, codes4, err2, ws_ck, P5, codes5, err5
-            ws_build = None
+            del err2
     del ws_build
     torch.cuda.empty_cache()
     log(f"prefill {prefill}")
