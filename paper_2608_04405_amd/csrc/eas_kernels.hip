@@ -132,9 +132,9 @@ struct TileSource {
   int n;
 };
 
-// Workgroup x: segment x % nseg of (b, h) = x / nseg.
-__global__ __launch_bounds__(kHardThreads, 8) void select_tile_kernel(TileSource src, int Hkv, int nseg, int seg,
-                                                                      int m, uint32_t* __restrict__ okey,
+// Workgroup (x, y): segment y of (b, h) = x (the y dimension is the one that is limited).
+__global__ __launch_bounds__(kHardThreads, 8) void select_tile_kernel(TileSource src, int Hkv, int seg, int m,
+                                                                      uint32_t* __restrict__ okey,
                                                                       int32_t* __restrict__ oidx, int64_t o_bh,
                                                                       int keep) {
   constexpr int NW = kHardThreads / 64;
@@ -143,7 +143,7 @@ __global__ __launch_bounds__(kHardThreads, 8) void select_tile_kernel(TileSource
   __shared__ int found[2];
   __shared__ uint32_t range[2];
   __shared__ int cnt_a[kTileRounds * NW], cnt_e[kTileRounds * NW];
-  const int bh = blockIdx.x / nseg, sidx = blockIdx.x % nseg, b = bh / Hkv, h = bh % Hkv;
+  const int bh = blockIdx.x, sidx = blockIdx.y, b = bh / Hkv, h = bh % Hkv;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int begin = sidx * seg, cnt = min(seg, src.n - begin);
   const int rounds = (cnt - t + kHardThreads - 1) / kHardThreads;  // this thread's keys: j < rounds
@@ -255,9 +255,8 @@ size_t select_hard_workspace_bytes(int B, int Hkv, int N, int m) {
 hipError_t launch_select_hard(const float* err, int64_t sE_b, int64_t sE_h, int B, int Hkv, int N, int m,
                               int32_t* out, void* ws, hipStream_t stream) {
   const size_t BH = (size_t)B * Hkv;
-  // one workgroup per segment in grid x, which takes 2^32 threads
-  const size_t wgs = BH * ((N + tile_segment(N) - 1) / tile_segment(N));
-  if (m > 0 && m <= kTileMost && N > kTileLeast && (N <= kTileKeys || ws) && wgs < (1ull << 32) / kHardThreads) {
+  const int segments = (N + tile_segment(N) - 1) / tile_segment(N);
+  if (m > 0 && m <= kTileMost && N > kTileLeast && (N <= kTileKeys || ws) && segments < 65536) {
     TileSource src{reinterpret_cast<const uint32_t*>(err), sE_b, sE_h, nullptr, N};
     uint32_t* list = static_cast<uint32_t*>(ws);
     while (src.n > kTileKeys) {
@@ -265,13 +264,13 @@ hipError_t launch_select_hard(const float* err, int64_t sE_b, int64_t sE_h, int 
       const int64_t per = (int64_t)S * m;  // list entries per (b, h); only the last segment may keep fewer than m
       uint32_t* okey = list;
       int32_t* oidx = reinterpret_cast<int32_t*>(list + BH * per);
-      select_tile_kernel<<<(unsigned)(BH * S), kHardThreads, 0, stream>>>(src, Hkv, S, seg, m, okey, oidx, per, m);
+      select_tile_kernel<<<dim3((unsigned)BH, S), kHardThreads, 0, stream>>>(src, Hkv, seg, m, okey, oidx, per, m);
       const int last = src.n - (S - 1) * seg;
       src = TileSource{okey, (int64_t)Hkv * per, per, oidx, (int)((S - 1) * m + (last < m ? last : m))};
       // (the next level writes past this list, the one after that over the first)
       list = list == static_cast<uint32_t*>(ws) ? list + 2 * BH * per : static_cast<uint32_t*>(ws);
     }
-    select_tile_kernel<<<(unsigned)BH, kHardThreads, 0, stream>>>(src, Hkv, 1, kTileKeys, m, nullptr, out, m, 0);
+    select_tile_kernel<<<(unsigned)BH, kHardThreads, 0, stream>>>(src, Hkv, kTileKeys, m, nullptr, out, m, 0);
     return hipGetLastError();
   }
   if (m > 0) select_hard_kernel<<<B * Hkv, kHardThreads, 0, stream>>>(err, sE_b, sE_h, Hkv, N, m, out);
