@@ -54,11 +54,12 @@
 //
 // What bounds it: vector issue and LDS reads (each block's triangle of
 // corrections, its operands read uniformly from LDS), at two wavefronts per
-// SIMD.  Batch 16 x 8 heads x 131072 keys, L = 64: 2.44 ms (2.67 before the
+// SIMD.  Batch 16 x 8 heads x 131072 keys, L = 64: 1.90 ms (2.67 before the
 // parts of P were cut once per workgroup, the certificate was folded into one
 // multiply-add per bit, the next tile's keys were loaded during the last block's
-// decisions and the set-up moved to the fp64 matrix cores); 8 x 1048576 keys,
-// L = 128: 4.41 ms (5.40); 8 x 8192 keys, L = 64, mostly set-up: 40 us (64).
+// decisions and the set-up moved to the fp64 matrix cores; of these 0.5 came when
+// 20 registers were no longer spilled); 8 x 1048576 keys, L = 128: 4.4 ms (5.40);
+// 8 x 8192 keys, L = 64, mostly set-up: 32 us (64).
 
 #include "bpc_internal.h"
 #include "mfma_split.h"
