@@ -632,9 +632,11 @@ __device__ __forceinline__ void two_sum(double a, double b, double& s, double& e
 // as the sign pass does.  Bound by vector issue (four instructions per key and
 // bit) on one compute unit.  A column of a million keys at L = 128: 4 to 7 ms (8
 // to 15 with a chunk per lane, each reading its bytes of every plane); the whole
-// build of 8 x 1048576 keys 105 -> 82 ms.
+// build of 8 x 1048576 keys 105 -> 82 ms.  A function of its own, so that the solves
+// that do not need it (all but a few) keep their code short: 8 x 8192 keys, L = 64,
+// 1062 -> 1036 us.
 template <int W, int NTH>
-__device__ double reference_column(const uint16_t* Kd, int64_t sK_n, const uint64_t* planes, int N, int bit,
+__device__ __noinline__ double reference_column(const uint16_t* Kd, int64_t sK_n, const uint64_t* planes, int N, int bit,
                                    const double* pcol, double* node) {
   constexpr int NP = W == 4 ? 2 : 1;
   constexpr int Q = 8;  // blocks per turn
